@@ -5,7 +5,8 @@
 // the transpose, out^T = A^T x in^T, so that
 //   * the MFMA "A" operand (M x K) is the core, M = output bond index,
 //   * the MFMA "B" operand (K x N) holds the activations, N = 16 rows,
-//   * the 16 x 16 result tile (M x N) gives 16 output features of 16 rows.
+//   * the 16 x 16 result tile (M x N) gives 16 output features (frag_feature)
+//     of 16 rows.
 // Lane l of a wave works on row n = l % 16 and K-group g = l / 16.  For a
 // row, group g owns the contiguous input features [g*chi/4, (g+1)*chi/4);
 // core fragments are pre-swizzled on the host so that each lane's share of
@@ -21,6 +22,7 @@ namespace rttk {
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------- BF16 bits
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float x) {
@@ -45,10 +47,20 @@ __device__ __forceinline__ void split_bf16x2(float a, float b, uint32_t& hi, uin
   lo = pack_bf16x2(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
 }
 
+// ---------------------------------------------------------------- fragments
+// A lane's KPL core elements of one tile, kept as the 32-bit words they are
+// loaded as (one FP32 value, two BF16 values or four FP8 codes each), which
+// is how the matrix ops and the FP8 decode take them.
+template <class E, int KPL>
+struct Frag {
+  static constexpr int NW = KPL * (int)sizeof(E) / 4;
+  uint32_t w[NW];
+};
+
 // ---------------------------------------------------------------- dtype traits
 // Storage element of packed cores and the K-loop of one 16x16 output tile.
 // prep() turns a lane's KPL FP32 activations into MFMA B operands once;
-// mma() / mma2() run the K loop for one (or two, interleaved) core slices.
+// mma() runs the K loop for one core slice.
 struct DF32 {
   using elem = float;
   static constexpr bool kF32 = true;  // FP32 activations on FP32 matrix ops
@@ -60,22 +72,12 @@ struct DF32 {
     for (int c = 0; c < KPL; ++c) b.v[c] = x[c];
   }
   template <int KPL>
-  __device__ __forceinline__ static f4 mma(const float (&a)[KPL], const BOp<KPL>& b, f4 acc) {
+  __device__ __forceinline__ static f4 mma(const Frag<float, KPL>& a, const BOp<KPL>& b, f4 acc) {
 #pragma unroll
     for (int c = 0; c < KPL; ++c)
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c], b.v[c], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w[c]), b.v[c], acc, 0, 0, 0);
     return acc;
   }
-  template <int KPL>
-  __device__ __forceinline__ static void mma2(const float (&a0)[KPL], const float (&a1)[KPL],
-                                              const BOp<KPL>& b, f4& c0, f4& c1) {
-#pragma unroll
-    for (int c = 0; c < KPL; ++c) {
-      c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[c], b.v[c], c0, 0, 0, 0);
-      c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[c], b.v[c], c1, 0, 0, 0);
-    }
-  }
-  __device__ __forceinline__ static float to_f32(float x) { return x; }
 };
 
 // BF16 cores.  FP32 activations enter the matrix cores as a hi + lo BF16
@@ -99,14 +101,12 @@ struct DBF16 {
     }
   }
   template <int KPL>
-  __device__ __forceinline__ static bf16x8 pack(const uint16_t (&a)[KPL], int c) {
-    u16x8 av;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) av[i] = a[8 * c + i];
-    return __builtin_bit_cast(bf16x8, av);
+  __device__ __forceinline__ static bf16x8 pack(const Frag<uint16_t, KPL>& a, int c) {
+    const u32x4 v = {a.w[4 * c], a.w[4 * c + 1], a.w[4 * c + 2], a.w[4 * c + 3]};
+    return __builtin_bit_cast(bf16x8, v);
   }
   template <int KPL>
-  __device__ __forceinline__ static f4 mma(const uint16_t (&a)[KPL], const BOp<KPL>& b, f4 acc) {
+  __device__ __forceinline__ static f4 mma(const Frag<uint16_t, KPL>& a, const BOp<KPL>& b, f4 acc) {
 #pragma unroll
     for (int c = 0; c < KPL / 8; ++c) {
       const bf16x8 av = pack<KPL>(a, c);
@@ -115,19 +115,6 @@ struct DBF16 {
     }
     return acc;
   }
-  template <int KPL>
-  __device__ __forceinline__ static void mma2(const uint16_t (&a0)[KPL], const uint16_t (&a1)[KPL],
-                                              const BOp<KPL>& b, f4& c0, f4& c1) {
-#pragma unroll
-    for (int c = 0; c < KPL / 8; ++c) {
-      const bf16x8 x0 = pack<KPL>(a0, c), x1 = pack<KPL>(a1, c);
-      c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0, b.hi[c], c0, 0, 0, 0);
-      c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x1, b.hi[c], c1, 0, 0, 0);
-      c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0, b.lo[c], c0, 0, 0, 0);
-      c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x1, b.lo[c], c1, 0, 0, 0);
-    }
-  }
-  __device__ __forceinline__ static float to_f32(uint16_t x) { return bf16_to_f32(x); }
 };
 
 // FP8 cores: one OCP e4m3 code per byte.  The matrix ops take a code c as
@@ -143,10 +130,10 @@ constexpr float kFp8Scale = 0.001953125f;  // 2^-9
 struct DFP8 {
   using elem = uint8_t;
   static constexpr bool kF32 = false;
-  // a lane's KPL codes decoded to BF16 bits (for fragments that serve many
+  // a lane's KPL codes decoded to BF16 values (for fragments that serve many
   // matrix ops: decode once, then run them as BF16)
   template <int KPL>
-  __device__ __forceinline__ static void decode(const uint8_t (&a)[KPL], uint16_t (&out)[KPL]);
+  __device__ __forceinline__ static void decode(const Frag<uint8_t, KPL>& a, Frag<uint16_t, KPL>& out);
   template <int KPL>
   using BOp = DBF16::BOp<KPL>;
   template <int KPL>
@@ -155,25 +142,17 @@ struct DFP8 {
   }
   // the 8 codes at elements 8c .. 8c+7 of a lane's fragment as BF16 values
   template <int KPL>
-  __device__ __forceinline__ static bf16x8 pack(const uint8_t (&a)[KPL], int c) {
+  __device__ __forceinline__ static bf16x8 pack(const Frag<uint8_t, KPL>& a, int c) {
     typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-    uint32_t w0 = 0, w1 = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      w0 |= (uint32_t)a[8 * c + i] << (8 * i);
-      w1 |= (uint32_t)a[8 * c + 4 + i] << (8 * i);
-    }
+    const uint32_t w0 = a.w[2 * c], w1 = a.w[2 * c + 1];
     const b2 p0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, kFp8Scale, false);
     const b2 p1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, kFp8Scale, true);
     const b2 p2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, kFp8Scale, false);
     const b2 p3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, kFp8Scale, true);
     return bf16x8{p0[0], p0[1], p1[0], p1[1], p2[0], p2[1], p3[0], p3[1]};
   }
-  __device__ __forceinline__ static float to_f32(uint8_t x) {
-    return (float)__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((uint32_t)x, kFp8Scale, false)[0];
-  }
   template <int KPL>
-  __device__ __forceinline__ static f4 mma(const uint8_t (&a)[KPL], const BOp<KPL>& b, f4 acc) {
+  __device__ __forceinline__ static f4 mma(const Frag<uint8_t, KPL>& a, const BOp<KPL>& b, f4 acc) {
 #pragma unroll
     for (int c = 0; c < KPL / 8; ++c) {
       const bf16x8 av = pack<KPL>(a, c);
@@ -182,29 +161,27 @@ struct DFP8 {
     }
     return acc;
   }
-  template <int KPL>
-  __device__ __forceinline__ static void mma2(const uint8_t (&a0)[KPL], const uint8_t (&a1)[KPL],
-                                              const BOp<KPL>& b, f4& c0, f4& c1) {
-#pragma unroll
-    for (int c = 0; c < KPL / 8; ++c) {
-      const bf16x8 x0 = pack<KPL>(a0, c), x1 = pack<KPL>(a1, c);
-      c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0, b.hi[c], c0, 0, 0, 0);
-      c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x1, b.hi[c], c1, 0, 0, 0);
-      c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0, b.lo[c], c0, 0, 0, 0);
-      c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x1, b.lo[c], c1, 0, 0, 0);
-    }
-  }
 };
 
 template <int KPL>
-__device__ __forceinline__ void DFP8::decode(const uint8_t (&a)[KPL], uint16_t (&out)[KPL]) {
+__device__ __forceinline__ void DFP8::decode(const Frag<uint8_t, KPL>& a, Frag<uint16_t, KPL>& out) {
 #pragma unroll
   for (int c = 0; c < KPL / 8; ++c) {
-    const u16x8 v = __builtin_bit_cast(u16x8, pack<KPL>(a, c));
+    const u32x4 v = __builtin_bit_cast(u32x4, pack<KPL>(a, c));
 #pragma unroll
-    for (int i = 0; i < 8; ++i) out[8 * c + i] = v[i];
+    for (int i = 0; i < 4; ++i) out.w[4 * c + i] = v[i];
   }
 }
+
+// Vector, matrix and global memory instructions keep their side of this point
+// (scalar and LDS ones may cross it): the order written down is the order
+// issued.
+__device__ __forceinline__ void hold_order() { __builtin_amdgcn_sched_barrier(0x784); }
+
+// Only loads and matrix ops keep their side of this point: the scheduler
+// otherwise sinks a prefetch to just before its use, where the whole latency
+// is waited for.
+__device__ __forceinline__ void hold_loads() { __builtin_amdgcn_sched_barrier(0x786); }
 
 // Workgroup barrier that orders LDS only: global loads issued before it
 // (prefetched core fragments) stay in flight across it.
@@ -222,6 +199,11 @@ __device__ __forceinline__ void lds_barrier() {
 __host__ __device__ constexpr size_t frag_offset(int lane, int e, int ce) {
   return ((size_t)(e / ce) * 64 + lane) * ce + e % ce;
 }
+// The output feature in row m of tile t.  A product leaves lane group m / 4
+// with rows 4 (m / 4) .. + 3 of every tile, and the next one takes from lane
+// group g the features [g kpl, (g + 1) kpl): rows are numbered so that these
+// are the same features.
+__host__ __device__ constexpr int frag_feature(int t, int m, int kpl) { return (m >> 2) * kpl + 4 * t + (m & 3); }
 // chunk length in elements: 16 bytes, or a lane's whole fragment when that is
 // shorter (FP8 at bond 32: 8 codes, one 8-byte load)
 __host__ __device__ constexpr int frag_chunk(int elem_bytes, int kpl) {
@@ -229,46 +211,50 @@ __host__ __device__ constexpr int frag_chunk(int elem_bytes, int kpl) {
 }
 
 // Load a lane's KPL-element fragment from a tile (16-byte aligned).
-template <int KPL>
-__device__ __forceinline__ void load_frag(float (&dst)[KPL], const float* tile, int lane) {
-  const float4* s = reinterpret_cast<const float4*>(tile) + lane;
+template <class E, int KPL>
+__device__ __forceinline__ void load_frag(Frag<E, KPL>& dst, const E* tile, int lane) {
+  constexpr int NW = Frag<E, KPL>::NW;
+  if constexpr (NW % 4 == 0) {
+    const u32x4* s = reinterpret_cast<const u32x4*>(tile) + lane;
 #pragma unroll
-  for (int i = 0; i < KPL / 4; ++i) {
-    float4 v = s[64 * i];
-    dst[4 * i + 0] = v.x; dst[4 * i + 1] = v.y; dst[4 * i + 2] = v.z; dst[4 * i + 3] = v.w;
-  }
-}
-template <int KPL>
-__device__ __forceinline__ void load_frag(uint16_t (&dst)[KPL], const uint16_t* tile, int lane) {
-  const uint4* s = reinterpret_cast<const uint4*>(tile) + lane;
+    for (int i = 0; i < NW / 4; ++i) {
+      const u32x4 v = s[64 * i];
 #pragma unroll
-  for (int i = 0; i < KPL / 8; ++i) {
-    uint4 v = s[64 * i];
-    uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      dst[8 * i + 2 * j] = (uint16_t)(w[j] & 0xffffu);
-      dst[8 * i + 2 * j + 1] = (uint16_t)(w[j] >> 16);
+      for (int j = 0; j < 4; ++j) dst.w[4 * i + j] = v[j];
     }
+  } else {
+    static_assert(NW == 2, "FP8 fragments of 8 or a multiple of 16 codes per lane");
+    const uint2 v = reinterpret_cast<const uint2*>(tile)[lane];
+    dst.w[0] = v.x;
+    dst.w[1] = v.y;
   }
 }
 
-template <int KPL>
-__device__ __forceinline__ void load_frag(uint8_t (&dst)[KPL], const uint8_t* tile, int lane) {
-  if constexpr (KPL % 16 == 0) {
-    const uint4* s = reinterpret_cast<const uint4*>(tile) + lane;
+// The same tile of both slices (global memory), word by word in the order the
+// matrix ops take them: a wait for the first words does not then cover the last.
+template <class E, int KPL>
+__device__ __forceinline__ void load_frag2(Frag<E, KPL> (&dst)[2], const __attribute__((address_space(1))) char* tile0,
+                                           const __attribute__((address_space(1))) char* tile1, int lane) {
+  constexpr int NW = Frag<E, KPL>::NW;
+  if constexpr (NW % 4 == 0) {
+    typedef const __attribute__((address_space(1))) u32x4* gvec;
 #pragma unroll
-    for (int i = 0; i < KPL / 16; ++i) {
-      uint4 v = s[64 * i];
-      uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    for (int i = 0; i < NW / 4; ++i)
 #pragma unroll
-      for (int j = 0; j < 16; ++j) dst[16 * i + j] = (uint8_t)(w[j / 4] >> (8 * (j % 4)));
-    }
+      for (int q = 0; q < 2; ++q) {
+        const u32x4 v = ((gvec)(q ? tile1 : tile0))[64 * i + lane];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) dst[q].w[4 * i + j] = v[j];
+      }
   } else {
-    static_assert(KPL == 8, "FP8 fragments of 8 or a multiple of 16 codes per lane");
-    const uint2 v = reinterpret_cast<const uint2*>(tile)[lane];
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    typedef const __attribute__((address_space(1))) u32x2* gvec;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) dst[j] = (uint8_t)((j < 4 ? v.x : v.y) >> (8 * (j % 4)));
+    for (int q = 0; q < 2; ++q) {
+      const u32x2 v = ((gvec)(q ? tile1 : tile0))[lane];
+      dst[q].w[0] = v[0];
+      dst[q].w[1] = v[1];
+    }
   }
 }
 

@@ -16,7 +16,8 @@
 #include <vector>
 
 #include "../../include/rtt.h"
-#include "rtt_kernels.hpp"
+#include "rtt_estimators.hpp"
+#include "rtt_host.hpp"
 #include "rtt_narrow.hpp"
 #include "rtt_net.hpp"
 #include "rtt_tt.hpp"
@@ -25,7 +26,9 @@ namespace {
 
 thread_local std::string g_err;
 
-rtt_status fail(rtt_status st, const char* fmt, ...) {
+}  // namespace
+
+rtt_status rtt_host::fail(rtt_status st, const char* fmt, ...) {
   char buf[512];
   va_list ap;
   va_start(ap, fmt);
@@ -35,15 +38,12 @@ rtt_status fail(rtt_status st, const char* fmt, ...) {
   return st;
 }
 
-#define HIPX(call)                                                                   \
-  do {                                                                               \
-    hipError_t e_ = (call);                                                          \
-    if (e_ != hipSuccess)                                                            \
-      return fail(e_ == hipErrorOutOfMemory ? RTT_E_OOM : RTT_E_HIP, "%s: %s (%s:%d)", \
-                  #call, hipGetErrorString(e_), __FILE__, __LINE__);                 \
-  } while (0)
+using rtt_host::fail;
 
-constexpr size_t kLdsLimit = 160 * 1024;
+namespace {
+
+using namespace rtt_host;
+
 constexpr int kPassOccupancy = 2;  // pass blocks per CU worth trading extra row groups for
 
 // ------------------------------------------------------------------ quantisation
@@ -177,28 +177,6 @@ Sched build_sched(const std::vector<int>& pi, int N, int L, int c, int ng) {
   return s;
 }
 
-int rttk_wpw(int chi) { return chi >= 64 ? 4 : chi / 16; }
-
-// the passes of rttk::pass_wide_form run the K-outer form (rows in place
-// when so built, and at most kPassWideTiles row tiles per walker)
-bool pass_wide(int dtype, int chi) {
-  return PASS_W_ENABLE && ((dtype == RTT_FP8_E4M3 && (chi == 256 || (PASS_W_128 && chi == 128))) ||
-                           (dtype == RTT_BF16 && PASS_W_128 && chi == 128));
-}
-int pass_max_slots(int dtype, int chi) { return pass_wide(dtype, chi) ? 16 * rttk::kPassWideTiles : 1 << 30; }
-
-size_t pass_lds_bytes(int chi, int nslot, int nw, int dtype) {
-  const int wpw = chi >= 64 ? 4 : chi / 16;
-  const int wpb = 4 / wpw;
-  const size_t rs = chi + 4;
-  const int nb = (pass_wide(dtype, chi) && rttk::kPassWideInPlace) ? 1 : 2;  // row buffers
-  return (size_t)wpb * (nb * nslot * rs * 4 + nb * nslot * 4 + nw * 8);
-}
-
-size_t chain_lds_bytes(int chi, int T, int L, int nw, int n_spins, int cg = 1) {
-  return (size_t)rttk::ChainLayout(chi, T, (L + 63) / 64, nw, cg, 0, n_spins).total;
-}
-
 }  // namespace
 
 struct rtt_s {
@@ -211,7 +189,7 @@ struct rtt_s {
   std::vector<int> cesum;                   // [T][L+1] prefix sums of core_exp
   std::vector<uint64_t> rmask;              // [N][LW] replica positions of each spin
   Sched sched;
-  std::vector<int> order, first;
+  std::vector<int> order, first, last;
   // device
   void* d_fwd = nullptr;      // [T][L][2][chi*chi] transposed fragments
   void* d_bwd = nullptr;      // [T][L][2][chi*chi]
@@ -228,6 +206,7 @@ struct rtt_s {
   int* d_pi = nullptr;
   int* d_order = nullptr;
   int* d_first = nullptr;
+  int* d_last = nullptr;
   double* d_coeffs = nullptr;
   // narrow-bond path (every bond <= 4): C x C slices, prescaled, zero padded
   int narrow = 0;             // C = 2 or 4, 0 when the matrix-core path runs
@@ -239,7 +218,7 @@ struct rtt_s {
   float* d_v = nullptr;
   int* d_ue = nullptr;
   int* d_ve = nullptr;
-  float* d_ck = nullptr;      // global column checkpoints of the sequential sampler layout
+  void* d_ck = nullptr;       // sampler vectors in global memory: column checkpoints, then prefixes
   size_t ck_bytes = 0;
   // this state's amplitudes and local energies as a dual Monte Carlo target
   size_t mix_W = 0;
@@ -260,9 +239,9 @@ namespace {
 size_t elem_bytes(int dtype) { return dtype == RTT_F32 ? 4 : dtype == RTT_BF16 ? 2 : 1; }
 
 // Pack one term: element (t, lane, e) of slice (k, b) in the forward layout
-// is core[b][g*KPL + e][16t + m] (transposed), in the backward layout
-// core[b][16t + m][g*KPL + e]; lane = 16 g + m, KPL = chi / 4.  Within the
-// 64 * KPL elements of tile t the order is rttk::frag_offset's.  Elements are
+// is core[b][g*KPL + e][f] (transposed), in the backward layout
+// core[b][f][g*KPL + e]; lane = 16 g + m, KPL = chi / 4, f =
+// rttk::frag_feature(t, m, KPL).  Within the 64 * KPL elements of tile t the order is rttk::frag_offset's.  Elements are
 // the quantised core divided by 2^core_exp: FP32 and BF16 values, or for FP8
 // the e4m3 code c of the value c * 2^-9 (core_exp = FP8 scale + 9).
 void pack_term(const rtt_s* h, int term, const std::vector<double>& q, std::vector<uint8_t>& fw,
@@ -289,8 +268,9 @@ void pack_term(const rtt_s* h, int term, const std::vector<double>& q, std::vect
           for (int e = 0; e < KPL; ++e) {
             const int g = lane >> 4, m = lane & 15;
             const size_t idx = base + (size_t)t * 64 * KPL + rttk::frag_offset(lane, e, rttk::frag_chunk((int)eb, KPL));
-            const double vf = pad[s * slice + (size_t)(g * KPL + e) * chi + 16 * t + m];
-            const double vb = pad[s * slice + (size_t)(16 * t + m) * chi + g * KPL + e];
+            const int f = rttk::frag_feature(t, m, KPL);
+            const double vf = pad[s * slice + (size_t)(g * KPL + e) * chi + f];
+            const double vb = pad[s * slice + (size_t)f * chi + g * KPL + e];
             if (eb == 4) {
               const float ff = (float)vf, fb = (float)vb;
               memcpy(&fw[idx * 4], &ff, 4);
@@ -320,7 +300,7 @@ rtt_status upload(void** dst, const void* src, size_t bytes) {
 // workspace came from the stream-ordered allocator and goes back to it.
 void free_dev(rtt_s* h) {
   void* ptrs[] = {h->d_grp, h->d_fgs, h->d_bgs, h->d_fwd, h->d_bwd, h->d_cexp, h->d_cesum, h->d_rmask, h->d_sf, h->d_sb, h->d_fslot, h->d_bslot,
-                  h->d_pi, h->d_order, h->d_first, h->d_coeffs, h->d_ncores};
+                  h->d_pi, h->d_order, h->d_first, h->d_last, h->d_coeffs, h->d_ncores};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   void* ws[] = {h->d_u, h->d_v, h->d_ue, h->d_ve, h->d_mla, h->d_msg, h->d_mel, h->d_mst, h->d_ck};
@@ -439,13 +419,15 @@ rtt_status finish_create(rtt_s* h) {
     }
   }
   if (!have) return fail(RTT_E_UNSUPPORTED, "rtt_create: flip-ratio rows of one walker exceed on-chip memory");
-  if (chain_lds_bytes(h->chi, h->T, h->L, h->nw, h->N) > kLdsLimit)
+  if (CheckpointRule(h->chi, h->T, LW, h->nw, 0, h->N).total > kLdsLimit)
     return fail(RTT_E_UNSUPPORTED, "rtt_create: sampling state of 16 walkers exceeds on-chip memory");
   h->sched = best;
   // proposal order: spins by first position, unread spins last
   h->first.assign(h->N, -1);
   for (int k = 0; k < h->L; ++k)
     if (h->first[h->pi[k]] < 0) h->first[h->pi[k]] = k;
+  h->last.assign(h->N, -1);
+  for (int k = 0; k < h->L; ++k) h->last[h->pi[k]] = k;
   h->order.clear();
   for (int k = 0; k < h->L; ++k)
     if (h->first[h->pi[k]] == k) h->order.push_back(h->pi[k]);
@@ -475,6 +457,7 @@ rtt_status finish_create(rtt_s* h) {
   if ((st = upload((void**)&h->d_pi, h->pi.data(), h->pi.size() * 4)) != RTT_OK) return st;
   if ((st = upload((void**)&h->d_order, h->order.data(), h->order.size() * 4)) != RTT_OK) return st;
   if ((st = upload((void**)&h->d_first, h->first.data(), h->first.size() * 4)) != RTT_OK) return st;
+  if ((st = upload((void**)&h->d_last, h->last.data(), h->last.size() * 4)) != RTT_OK) return st;
   if ((st = upload((void**)&h->d_coeffs, h->coeffs.data(), h->coeffs.size() * 8)) != RTT_OK) return st;
   if ((st = setup_narrow(h)) != RTT_OK) return st;
   const char* ck = getenv("RTT_CHAIN_CHECKPOINTS");
@@ -508,137 +491,6 @@ rtt_status ensure_ws(rtt_s* h, int W, hipStream_t s) {
   return RTT_OK;
 }
 
-// ------------------------------------------------------------------ dispatch
-template <class D, int CHI>
-rtt_status launch_pass(const rttk::PassArgs& a, int T, hipStream_t s) {
-  constexpr int WPW = rttk::Geo<CHI>::WPW;
-  constexpr int WPB = 4 / WPW;
-  const size_t lds = pass_lds_bytes(CHI, a.nslot, a.nw,
-                                    std::is_same<D, rttk::DFP8>::value    ? RTT_FP8_E4M3
-                                    : std::is_same<D, rttk::DBF16>::value ? RTT_BF16
-                                                                          : RTT_F32);
-  auto kfn = rttk::pass_kernel<D, CHI>;
-  HIPX(hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  dim3 grid((a.W + WPB - 1) / WPB, T);
-  hipLaunchKernelGGL(kfn, grid, dim3(256), lds, s, a);
-  HIPX(hipGetLastError());
-  return RTT_OK;
-}
-
-int device_cus() {
-  int dev = 0, n = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 256;
-  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 256;
-  return n;
-}
-
-// Column checkpoints for a sweep launch: as many as fit in the LDS left over
-// (without lowering the blocks per CU the launch needs, at most 16), evenly
-// spaced over the bonds a proposal can start its columns from, [lo, L), lo
-// being passed in ck_first.
-void chain_checkpoints(rttk::ChainArgs& a, int chi, int cg, int blocks) {
-  const int lo = a.ck_first, LW = (a.L + 63) / 64;
-  a.n_ck = 0; a.ck_first = 0; a.ck_step = 1;
-  if (a.mode != 1 || lo >= a.L || lo < 1) return;
-  const rttk::ChainLayout l0(chi, a.T, LW, a.nw, cg, 0, a.N);
-  int nmax = 0;
-  if (l0.seq) {
-    // sequential layout (bond 256, one block per CU): the vectors go to the
-    // global buffer, only their exponents take LDS
-    if (chi != 256 || cg != 1 || !a.ckg) return;
-    for (int n = std::min(16, a.ck_cap); n >= 1 && nmax == 0; --n)
-      if ((size_t)rttk::ChainLayout(chi, a.T, LW, a.nw, cg, n, a.N).total <= kLdsLimit) nmax = n;
-  } else {
-    if (chi > 64) return;
-    const size_t budget = kLdsLimit / (blocks > device_cus() ? 2 : 1);
-    // the largest count whose layout fits, preferring counts that keep the
-    // replica bitmasks in LDS as they are without checkpoints (each layout is
-    // sized in full: the masks may stop fitting as checkpoints are added)
-    for (int pass = 0; pass < 2 && nmax == 0; ++pass)
-      for (int n = 16; n >= 1; --n) {
-        const rttk::ChainLayout ln(chi, a.T, LW, a.nw, cg, n, a.N);
-        if ((size_t)ln.total <= budget && (pass == 1 || ln.rml == l0.rml)) { nmax = n; break; }
-      }
-  }
-  if (nmax < 1) return;
-  const int span = a.L - lo;
-  const int step = (span + nmax - 1) / nmax;
-  a.n_ck = (span + step - 1) / step;
-  a.ck_first = lo;
-  a.ck_step = step;
-}
-
-template <class D, int CHI, int CG>
-rtt_status launch_chain_cg(const rttk::ChainArgs& a0, hipStream_t s) {
-  rttk::ChainArgs a = a0;
-  dim3 grid((a.W + 16 * CG - 1) / (16 * CG));
-  chain_checkpoints(a, CHI, CG, (int)grid.x);
-  const size_t lds = (size_t)rttk::ChainLayout(CHI, a.T, (a.L + 63) / 64, a.nw, CG, a.n_ck, a.N).total;
-  auto kfn = rttk::chain_kernel<D, CHI, CG, false>;
-  // (at bond 256 only the FP8 kernel fits the checkpoint code in registers;
-  // the BF16 one would spill)
-  if constexpr (CHI <= 64)
-    if (a.n_ck > 0) kfn = rttk::chain_kernel<D, CHI, CG, true>;
-  if constexpr (CHI == 256 && CG == 1 && std::is_same<D, rttk::DFP8>::value)
-    if (a.n_ck > 0) kfn = rttk::chain_kernel<D, CHI, CG, true, true>;   // sequential layout: vectors in global memory
-  HIPX(hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL(kfn, grid, dim3(rttk::ChainGeo<CHI, D>::NT), lds, s, a);
-  HIPX(hipGetLastError());
-  return RTT_OK;
-}
-
-// Bond 128 with enough walkers to give every CU a block of 32 runs two
-// column groups per block (each core fragment serves 32 walkers), if the
-// state still fits on chip in the same layout.  (At 256 the registers of a
-// second group would spill; at 64 and below two waves share each SIMD.)
-template <class D, int CHI>
-rtt_status launch_chain(const rttk::ChainArgs& a, hipStream_t s) {
-  if constexpr (CHI == 128) {
-    const int LW = (a.L + 63) / 64;
-    const rttk::ChainLayout l1(CHI, a.T, LW, a.nw, 1, 0, a.N), l2(CHI, a.T, LW, a.nw, 2, 0, a.N);
-    if (a.W >= 32 * device_cus() && l2.seq == l1.seq && (size_t)l2.total <= kLdsLimit)
-      return launch_chain_cg<D, CHI, 2>(a, s);
-  }
-  return launch_chain_cg<D, CHI, 1>(a, s);
-}
-
-template <template <class, int> class F, class... Args>
-rtt_status dispatch(int dtype, int chi, Args&&... args) {
-  if (dtype == RTT_F32) {
-    switch (chi) {
-      case 16: return F<rttk::DF32, 16>::run(args...);
-      case 32: return F<rttk::DF32, 32>::run(args...);
-      case 64: return F<rttk::DF32, 64>::run(args...);
-      case 128: return F<rttk::DF32, 128>::run(args...);
-    }
-  } else if (dtype == RTT_BF16) {
-    switch (chi) {
-      case 32: return F<rttk::DBF16, 32>::run(args...);
-      case 64: return F<rttk::DBF16, 64>::run(args...);
-      case 128: return F<rttk::DBF16, 128>::run(args...);
-      case 256: return F<rttk::DBF16, 256>::run(args...);
-    }
-  } else if (dtype == RTT_FP8_E4M3) {
-    switch (chi) {
-      case 32: return F<rttk::DFP8, 32>::run(args...);
-      case 64: return F<rttk::DFP8, 64>::run(args...);
-      case 128: return F<rttk::DFP8, 128>::run(args...);
-      case 256: return F<rttk::DFP8, 256>::run(args...);
-    }
-  }
-  return fail(RTT_E_UNSUPPORTED, "no kernel for dtype %d, padded bond %d", dtype, chi);
-}
-
-template <class D, int CHI>
-struct PassL {
-  static rtt_status run(const rttk::PassArgs& a, int T, hipStream_t s) { return launch_pass<D, CHI>(a, T, s); }
-};
-template <class D, int CHI>
-struct ChainL {
-  static rtt_status run(const rttk::ChainArgs& a, hipStream_t s) { return launch_chain<D, CHI>(a, s); }
-};
-
-// nearest-neighbour bonds (i, i + x) and (i, i + y); wrap bonds on sides >= 3
 std::vector<int2> tfim_bond_list(int Lx, int Ly, int periodic) {
   std::vector<int2> b;
   for (int y = 0; y < Ly; ++y)
@@ -918,8 +770,8 @@ rtt_status rtt_get_cores(rtt_t h, int32_t term, double* out) {
     for (int s = 0; s < 2; ++s)
       for (int i = 0; i < a; ++i)
         for (int j = 0; j < b; ++j) {
-          // forward layout holds core[s][i][j] at g*KPL+e = i, 16t+m = j
-          const int g = i / KPL, e = i % KPL, t = j / 16, m = j % 16;
+          // forward layout holds core[s][i][j] at g*KPL + e = i, frag_feature(t, m) = j
+          const int g = i / KPL, e = i % KPL, t = j % KPL / 4, m = j / KPL * 4 + j % 4;
           const size_t idx = ((size_t)k * 2 + s) * slice + (size_t)t * 64 * KPL +
                              rttk::frag_offset(16 * g + m, e, rttk::frag_chunk((int)eb, KPL));
           double v;
@@ -1010,14 +862,14 @@ rtt_status evaluate_on(rtt_t h, rtt_ham_t ham, int32_t W, const uint64_t* spins,
   pa.gsteps = h->d_fgs;
   pa.out_vec = ws.u;
   pa.out_exp = ws.ue;
-  if ((st = dispatch<PassL>(h->dtype, h->chi, pa, h->T * h->sched.ng, s)) != RTT_OK) return st;
+  if ((st = pass_launch(h->dtype)->run(h->chi, pa, h->T * h->sched.ng, s)) != RTT_OK) return st;
   // backward
   pa.cores = h->d_bwd;
   pa.sched = h->d_sb;
   pa.gsteps = h->d_bgs;
   pa.out_vec = ws.v;
   pa.out_exp = ws.ve;
-  if ((st = dispatch<PassL>(h->dtype, h->chi, pa, h->T * h->sched.ng, s)) != RTT_OK) return st;
+  if ((st = pass_launch(h->dtype)->run(h->chi, pa, h->T * h->sched.ng, s)) != RTT_OK) return st;
   rttk::CombineArgs ca{};
   ca.u = ws.u; ca.ue = ws.ue; ca.v = ws.v; ca.ve = ws.ve;
   ca.nsf = h->sched.nslot; ca.nsb = h->sched.nslot; ca.chi = h->chi; ca.T = h->T; ca.W = W;
@@ -1139,42 +991,43 @@ static rtt_status chain_common(rtt_t h, int32_t W, uint64_t* spins, double* loga
   ca.cores = h->d_fwd; ca.cores_bwd = h->d_bwd;
   ca.cesum = h->d_cesum;
   ca.rmask = h->d_rmask;
-  ca.pi = h->d_pi; ca.order = h->d_order; ca.first = h->d_first; ca.coeffs = h->d_coeffs;
+  ca.pi = h->d_pi; ca.order = h->d_order; ca.first = h->d_first; ca.last = h->d_last; ca.coeffs = h->d_coeffs;
   ca.T = h->T; ca.L = h->L; ca.N = h->N; ca.nw = h->nw; ca.LW = (h->L + 63) / 64; ca.W = W;
   ca.spins = spins; ca.logabs = logabs; ca.sign = sign; ca.accepts = accepts; ca.status = status;
   ca.seed = seed; ca.rstream = rstream; ca.sweep0 = sweep0; ca.n_sweeps = n_sweeps; ca.mode = mode;
-  // Sequential sampler layout at bond 256 with FP8 cores (the terms of a
-  // combination take turns): room for 8 column checkpoints per block in
-  // global memory, grown
-  // in stream order (8 checkpoints keep 0.72 of the dependent steps of
-  // contracting every proposal's columns from the right boundary on the
-  // 16x16 two-replica path; 16 would keep 0.70 at twice the memory)
+  // FP8 cores at bond 256: room for 8 column checkpoints per 16 walkers of a
+  // combination in global memory, grown in stream order (8 checkpoints keep
+  // 0.72 of the dependent steps of contracting every proposal's columns from
+  // the right boundary on the 16x16 two-replica path; 16 would keep 0.70 at
+  // twice the memory), and for the prefixes of blocks of 32 walkers
   ca.ckg = nullptr;
   ca.ck_cap = 0;
-  if (mode == 1 && h->chain_ck && h->chi == 256 && h->dtype == RTT_FP8_E4M3 &&
-      rttk::ChainLayout(h->chi, h->T, (h->L + 63) / 64, h->nw, 1, 0, h->N).seq) {
+  ca.pg = nullptr;
+  if (mode == 1 && h->chi == 256 && h->dtype == RTT_FP8_E4M3) {
     const int cap = 8;
-    const size_t need = (size_t)((W + 15) / 16) * 2 * cap * h->T * 16 * (h->chi + 4) * 4;
+    const bool seq = CheckpointRule(h->chi, h->T, (h->L + 63) / 64, h->nw, 0, h->N).seq;
+    const size_t vec = (size_t)(W + 31) / 32 * 32 * h->T * h->chi * 4;  // a vector of every walker and term
+    const size_t ck = h->chain_ck && seq ? 2 * cap * vec : 0;
+    const size_t need = ck + (chain_global_prefix(h->dtype, h->chi, W) ? 2 * vec : 0);
     if (need > h->ck_bytes) {
       h->ck_bytes = 0;
       rtt_status st = grow_async((void**)&h->d_ck, need, (hipStream_t)stream);
       if (st != RTT_OK) return st;
       h->ck_bytes = need;
     }
-    ca.ckg = h->d_ck;
-    ca.ck_cap = cap;
+    if (ck) {
+      ca.ckg = h->d_ck;
+      ca.ck_cap = cap;
+    }
+    if (need > ck) ca.pg = static_cast<char*>(h->d_ck) + ck;
   }
   // the lowest bond a proposal's columns can start from: one past the
   // smallest last position over the spins
-  {
-    std::vector<int> last(h->N, -1);
-    for (int k = 0; k < h->L; ++k) last[h->pi[k]] = k;
-    int lo = h->L;
-    for (int j = 0; j < h->N; ++j)
-      if (last[j] >= 0) lo = std::min(lo, last[j] + 1);
-    ca.ck_first = h->chain_ck ? lo : h->L;
-  }
-  return dispatch<ChainL>(h->dtype, h->chi, ca, (hipStream_t)stream);
+  int lo = h->L;
+  for (int j = 0; j < h->N; ++j)
+    if (h->last[j] >= 0) lo = std::min(lo, h->last[j] + 1);
+  ca.ck_first = h->chain_ck ? lo : h->L;
+  return chain_launch(h->dtype)->run(h->chi, ca, (hipStream_t)stream);
 }
 
 rtt_status rtt_amplitudes(rtt_t h, int32_t W, const uint64_t* spins, double* logabs, int8_t* sign,
@@ -1454,39 +1307,20 @@ struct rtt_batch_s {
 
 namespace {
 
-// Sampler tile of a class: 16 walkers per block, or 32 (two column groups
-// sharing every core fragment) at the bonds where that kernel fits in
-// registers (at 64 and 256 the second group's operands spill).
-constexpr bool batch_cg2(int chi) { return chi == 32 || chi == 128; }
-template <class D, int CHI>
-constexpr bool kBatchCG2 = batch_cg2(CHI);
-
-template <class D, int CHI>
-struct BatchL {
-  static rtt_status run(BatchClass& c, int* counters, const uint64_t* sweep0, int phase, hipStream_t s) {
-    auto kchain = rttk::chain_persistent<D, CHI, 1>;
-    if constexpr (kBatchCG2<D, CHI>)
-      if (c.cg == 2) kchain = rttk::chain_persistent<D, CHI, 2>;
-    if (phase == 2) {  // before capture: allow the dynamic LDS sizes
-      HIPX(hipFuncSetAttribute((const void*)kchain, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.chain_lds));
-      HIPX(hipFuncSetAttribute((const void*)rttk::pass_persistent<D, CHI>,
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.pass_lds));
-      return RTT_OK;
-    }
-    if (phase == 0) {
-      if (c.chain_items.empty()) return RTT_OK;
-      hipLaunchKernelGGL(kchain, dim3(c.grid_chain), dim3(rttk::ChainGeo<CHI, D>::NT), c.chain_lds, s, c.d_chain,
-                         c.d_chain_items, (int)c.chain_items.size(), counters, sweep0);
-    } else {
-      if (c.pass_items.empty()) return RTT_OK;
-      auto kfn = rttk::pass_persistent<D, CHI>;
-      hipLaunchKernelGGL(kfn, dim3(c.grid_pass), dim3(256), c.pass_lds, s, c.d_pass, c.d_pass_items,
-                         (int)c.pass_items.size(), counters);
-    }
-    HIPX(hipGetLastError());
-    return RTT_OK;
-  }
-};
+// the sampler (phase 0) or the flip-ratio passes (1) of a class; prepare:
+// only allow their LDS sizes
+rtt_status launch_class(const BatchClass& c, int phase, int* counter, const uint64_t* sweep0, bool prepare,
+                        hipStream_t s) {
+  BatchLaunch l{};
+  l.cg = c.cg; l.grid_chain = c.grid_chain; l.grid_pass = c.grid_pass;
+  l.chain_lds = c.chain_lds; l.pass_lds = c.pass_lds;
+  l.d_chain = c.d_chain; l.d_pass = c.d_pass;
+  l.d_chain_items = c.d_chain_items; l.d_pass_items = c.d_pass_items;
+  l.n_chain = (int)c.chain_items.size(); l.n_pass = (int)c.pass_items.size();
+  l.counter = counter; l.sweep0 = sweep0;
+  if (!prepare && !(phase == 0 ? l.n_chain : l.n_pass)) return RTT_OK;
+  return phase == 0 ? chain_launch(c.dtype)->batch(c.chi, l, prepare, s) : pass_launch(c.dtype)->batch(c.chi, l, prepare, s);
+}
 
 // persistent blocks per compute unit that the class's LDS allows
 int lds_occupancy(size_t lds) { return std::max(1, std::min(4, (int)(kLdsLimit / std::max<size_t>(lds, 1)))); }
@@ -1501,7 +1335,7 @@ void build_chain_items(const rtt_batch_s* b, BatchClass& c, int cg) {
   for (int mi = 0; mi < (int)c.members.size(); ++mi) {
     const rtt_s* h = b->rtts[c.members[mi]];
     const int W = b->W[c.members[mi]];
-    c.chain_lds = std::max(c.chain_lds, chain_lds_bytes(c.chi, h->T, h->L, h->nw, h->N, cg));
+    c.chain_lds = std::max(c.chain_lds, chain_launch(h->dtype)->batch_lds(h->chi, h->T, h->L, h->nw, cg));
     for (int t = 0; t < (W + 16 * cg - 1) / (16 * cg); ++t) c.chain_items.push_back(make_int4(mi, t, 0, 0));
   }
 }
@@ -1540,7 +1374,7 @@ rtt_status record_step(rtt_batch_s* b, int n_sweeps, double* esum, hipStream_t s
       for (int ci = 0; ci < nc; ++ci) {
         BatchClass& c = b->classes[ci];
         HIPX(hipStreamWaitEvent(c.stream, b->fork, 0));
-        rtt_status st = dispatch<BatchL>(c.dtype, c.chi, c, b->d_counters + 2 * ci + phase, b->d_sweep0, phase, c.stream);
+        rtt_status st = launch_class(c, phase, b->d_counters + 2 * ci + phase, b->d_sweep0, false, c.stream);
         if (st != RTT_OK) return st;
         HIPX(hipEventRecord(b->done[ci], c.stream));
       }
@@ -1548,7 +1382,7 @@ rtt_status record_step(rtt_batch_s* b, int n_sweeps, double* esum, hipStream_t s
     } else {
       for (int ci = 0; ci < nc; ++ci) {
         BatchClass& c = b->classes[ci];
-        rtt_status st = dispatch<BatchL>(c.dtype, c.chi, c, b->d_counters + 2 * ci + phase, b->d_sweep0, phase, s);
+        rtt_status st = launch_class(c, phase, b->d_counters + 2 * ci + phase, b->d_sweep0, false, s);
         if (st != RTT_OK) return st;
       }
     }
@@ -1581,8 +1415,8 @@ rtt_status capture(rtt_batch_s* b, int n_sweeps, double* esum) {
   if (st != RTT_OK) return st;
   size_grids(b);
   for (auto& c : b->classes) {
-    st = dispatch<BatchL>(c.dtype, c.chi, c, (int*)nullptr, (const uint64_t*)nullptr, 2, b->cap);
-    if (st != RTT_OK) return st;
+    for (int phase = 0; phase < 2; ++phase)
+      if ((st = launch_class(c, phase, nullptr, nullptr, true, b->cap)) != RTT_OK) return st;
   }
   HIPX(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));
   st = record_step(b, n_sweeps, esum, b->cap);
@@ -1718,7 +1552,7 @@ static rtt_status rtt_batch_create_impl(int32_t n, const rtt_t* rtts, const rtt_
       const int W = b->W[i];
       rttk::ChainArgs ca{};
       ca.cores = h->d_fwd; ca.cores_bwd = h->d_bwd; ca.cesum = h->d_cesum; ca.rmask = h->d_rmask; ca.pi = h->d_pi;
-      ca.order = h->d_order; ca.first = h->d_first; ca.coeffs = h->d_coeffs;
+      ca.order = h->d_order; ca.first = h->d_first; ca.last = h->d_last; ca.coeffs = h->d_coeffs;
       ca.T = h->T; ca.L = h->L; ca.N = h->N; ca.nw = h->nw; ca.LW = (h->L + 63) / 64; ca.W = W;
       ca.spins = b->spins[i]; ca.seed = seed; ca.rstream = (uint64_t)i; ca.mode = 1;
       c.chain.push_back(ca);
@@ -1746,13 +1580,11 @@ static rtt_status rtt_batch_create_impl(int32_t n, const rtt_t* rtts, const rtt_
           for (int bx = 0; bx < (W + wpb - 1) / wpb; ++bx) c.pass_items.push_back(make_int4(2 * mi + dir, bx, ty, 0));
     }
     // sampler tiles: 16 walkers per block; 32 allowed where every member's
-    // state fits on chip in the same layout (same results, bit for bit)
+    // state fits on chip (same results, bit for bit)
     c.cg_max = batch_cg2(c.chi) ? 2 : 1;
     for (int i : c.members) {
       const rtt_s* h = b->rtts[i];
-      const int LW = (h->L + 63) / 64;
-      const rttk::ChainLayout l1(c.chi, h->T, LW, h->nw, 1, 0, h->N), l2(c.chi, h->T, LW, h->nw, 2, 0, h->N);
-      if (l2.seq != l1.seq || (size_t)l2.total > kLdsLimit) c.cg_max = 1;
+      if (chain_launch(h->dtype)->batch_lds(h->chi, h->T, h->L, h->nw, 2) > kLdsLimit) c.cg_max = 1;
     }
     const char* tile = getenv("RTT_BATCH_TILE");
     build_chain_items(b, c, (tile && atoi(tile) == 32 && c.cg_max == 2) ? 2 : 1);
