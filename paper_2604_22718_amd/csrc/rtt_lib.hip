@@ -1792,26 +1792,29 @@ constexpr int kNetSlices = 32;  // first-stage slices of the gradient sum over s
 
 rtt_status net_grad_launch(rtt_net_s* n, int B, const uint64_t* spins, const int32_t* moves,
                            const float* accept_prob, float* grad, hipStream_t s) {
-  if (B > n->B_ws) {
+  // blocks: as many as run at once (each keeps its sums in registers over its
+  // share of the samples)
+  const size_t lds = rttk::net_grad_lds_bytes(n->N);
+  const int G = std::min(B, device_cus() * std::max(1, std::min(2, (int)(kLdsLimit / lds))));
+  if (G > n->B_ws) {
     n->B_ws = 0;
-    // per-sample gradients, then room for the slice sums of the reduction
-    rtt_status st = grow_async((void**)&n->d_partial, (size_t)(B + kNetSlices) * rttk::kNetParams * 4, s);
+    // the blocks' partial gradients, then room for the slice sums of the reduction
+    rtt_status st = grow_async((void**)&n->d_partial, (size_t)(G + kNetSlices) * rttk::kNetParams * 4, s);
     if (st != RTT_OK) return st;
-    n->B_ws = B;
+    n->B_ws = G;
   }
   rttk::NetGradArgs ga{};
   ga.P = n->d_infer; ga.Lx = n->Lx; ga.Ly = n->Ly; ga.nw = n->nw; ga.B = B;
   ga.spins = spins; ga.moves = moves; ga.accept_prob = accept_prob; ga.baseline = n->d_baseline;
   ga.partial = n->d_partial;
-  const size_t lds = rttk::net_grad_lds_bytes(n->N);
   rtt_status st = net_set_lds((const void*)rttk::net_grad_kernel, lds);
   if (st != RTT_OK) return st;
-  hipLaunchKernelGGL(rttk::net_grad_kernel, dim3(B), dim3(256), lds, s, ga);
+  hipLaunchKernelGGL(rttk::net_grad_kernel, dim3(G), dim3(256), lds, s, ga);
   HIPX(hipGetLastError());
-  const int S = std::min(B, kNetSlices);
-  float* slices = n->d_partial + (size_t)B * rttk::kNetParams;
+  const int S = std::min(G, kNetSlices);
+  float* slices = n->d_partial + (size_t)G * rttk::kNetParams;
   hipLaunchKernelGGL(rttk::net_reduce_slices_kernel, dim3((rttk::kNetParams + 255) / 256, S), dim3(256), 0, s,
-                     n->d_partial, B, S, slices);
+                     n->d_partial, G, S, slices);
   HIPX(hipGetLastError());
   hipLaunchKernelGGL(rttk::net_reduce_kernel, dim3((rttk::kNetParams + 255) / 256), dim3(256), 0, s,
                      slices, S, grad);

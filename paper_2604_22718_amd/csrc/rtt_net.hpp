@@ -62,56 +62,6 @@ __device__ __forceinline__ void conv_site(const float* __restrict__ W, const flo
   }
 }
 
-// Forward pass of one configuration.  lds: z[N], then three [32][N] buffers
-// A1, A2, A3 holding pre-activations, then o[9][N].  Returns pointer to o.
-__device__ inline float* net_forward_block(const float* __restrict__ P, const uint64_t* spins,
-                                           const NetGeo& g, float* lds) {
-  const int N = g.N, i = threadIdx.x;
-  const bool act = i < N;
-  float* z = lds;
-  float* A1 = z + 256;
-  float* A2 = A1 + kNetC * N;
-  float* A3 = A2 + kNetC * N;
-  float* o = A3 + kNetC * N;
-  if (act) z[i] = 1.f - 2.f * (float)spin_bit(spins, i);
-  __syncthreads();
-  float acc[kNetC];
-  if (act) {
-    conv_site<1>(P + oW1, P + ob1, z, false, g, acc);
-#pragma unroll
-    for (int co = 0; co < kNetC; ++co) A1[co * N + i] = acc[co];
-  }
-  __syncthreads();
-  if (act) {
-    conv_site<kNetC>(P + oW2, P + ob2, A1, true, g, acc);
-#pragma unroll
-    for (int co = 0; co < kNetC; ++co) A2[co * N + i] = acc[co];
-  }
-  __syncthreads();
-  if (act) {
-    conv_site<kNetC>(P + oW3, P + ob3, A2, true, g, acc);
-#pragma unroll
-    for (int co = 0; co < kNetC; ++co) A3[co * N + i] = acc[co];
-  }
-  __syncthreads();
-  if (act) {
-    float h[kNetC];
-#pragma unroll
-    for (int c = 0; c < kNetC; ++c) h[c] = silu_f(A3[c * N + i]);
-    for (int k = 0; k < 9; ++k) {
-      float s = P[obh + k];
-#pragma unroll
-      for (int c = 0; c < kNetC; ++c) s = fmaf(P[oWh + k * kNetC + c], h[c], s);
-      o[k * N + i] = s;
-    }
-  }
-  __syncthreads();
-  return o;
-}
-
-// LDS of the scalar forward (training kernel): z, A1..A3, o, log-probs, scratch
-__host__ __device__ inline size_t net_lds_bytes(int N) { return (size_t)(280 + 115 * N) * 4; }
-
 // ---------------------------------------------------------------- matrix-core forward
 // The two 32 -> 32 channel 3x3 layers as implicit GEMMs on the BF16 matrix
 // cores: out^T[co][site] = sum over taps t and input channels ci of
@@ -482,126 +432,293 @@ struct NetGradArgs {
   const int* moves;        // [B] c | k << 16 sampled at s_b
   const float* accept_prob;// [B]
   const double* baseline;  // device scalar
-  float* partial;          // [B][kNetParams] per-sample gradients
+  float* partial;          // [blocks][kNetParams] partial gradients
 };
 
-// Gradient of coef_b log q(c_b, k_b | s_b), coef_b = -(a_b k_b - baseline) / B.
-__global__ void __launch_bounds__(256) net_grad_kernel(NetGradArgs a) {
-  extern __shared__ __align__(16) float lds[];
-  NetGeo g;
-  g.init(a.Lx, a.Ly);
-  const int b = blockIdx.x, N = g.N, i = threadIdx.x;
-  const bool act = i < N;
-  float* o = net_forward_block(a.P, a.spins + (size_t)b * a.nw, g, lds);
-  float* z = lds;
-  float* A1 = z + 256;
-  float* A2 = A1 + kNetC * N;
-  float* A3 = A2 + kNetC * N;
-  float* G = o + 9 * N;                       // [32][N] gradient buffer
-  double* lc = reinterpret_cast<double*>(G + kNetC * N + (N & 1));
-  float* lk = reinterpret_cast<float*>(lc + N);
-  double* shd = reinterpret_cast<double*>(lk + 8 * N + ((8 * N) & 1));
-  float* shf = reinterpret_cast<float*>(shd + 4);
-  net_logprobs(o, g, lc, lk, shd, shf);
-  const int c = a.moves[b] & 0xffff, k = a.moves[b] >> 16;
-  const double coef = -((double)a.accept_prob[b] * k - *a.baseline) / a.B;
-  float* out = a.partial + (size_t)b * kNetParams;
-  // d loss / d o, written over o: channel 0 at every site, size channels at c
-  if (act) {
-    o[i] = (float)(coef * ((i == c ? 1.0 : 0.0) - exp(lc[i])));
-    for (int m = 0; m < 8; ++m)
-      o[(m + 1) * N + i] = (i == c) ? (float)(coef * ((m + 1 == k ? 1.0 : 0.0) - exp((double)lk[m * N + i]))) : 0.f;
-  }
-  __syncthreads();
-  // head: dWh[k][ch] = sum_i do[k][i] h3[ch][i], dbh[k] = sum_i do[k][i]
-  for (int p = i; p < 9 * kNetC + 9; p += 256) {
-    float s = 0.f;
-    if (p < 9 * kNetC) {
-      const int kk = p / kNetC, ch = p % kNetC;
-      for (int j = 0; j < N; ++j) s = fmaf(o[kk * N + j], silu_f(A3[ch * N + j]), s);
-      out[oWh + p] = s;
-    } else {
-      const int kk = p - 9 * kNetC;
-      for (int j = 0; j < N; ++j) s += o[kk * N + j];
-      out[obh + kk] = s;
+// Gradient of sum_b coef_b log q(c_b, k_b | s_b), coef_b = -(a_b k_b - baseline)
+// / B, on the FP32 matrix cores.  A block takes samples b, b + gridDim, ... and
+// keeps its sums of the weight gradients in registers over all of them; one
+// partial gradient per block then goes to memory (a gradient per sample was
+// 313 MB written and read back at 4096 samples).
+//   conv layers and their transposes: out[ch][site], 16 x 16 tiles, K = 9 taps
+//     x 32 channels;
+//   weight gradients: dW[co][ci][t] = sum_i da[co][i] h[ci][nb(i, t)], wave
+//     (co tile, ci tile), nine tap tiles, K = sites;
+//   head and first layer: their 9 outputs or taps padded to 16.
+// Activations are [site][32] floats in LDS, the 16-byte chunks of a row swizzled
+// by (site / 2) % 8 so that 16 consecutive sites read one chunk conflict-free.
+// Buffers: X0 a1 -> da1; X1 h1 -> a3 -> da3; X2 a2 -> da2; X3 h2 -> h1.
+// Matrix ops of 4096 samples at 10x10 take 330 us of all 1024 SIMDs; measured
+// 0.94 ms (one thread per site or weight, a gradient per sample: 3.5 ms with
+// the sum over samples), the rest being layer weights, LDS reads and barriers.
+__device__ __forceinline__ int gidx(int site, int ch) {
+  return site * kNetC + ((((ch >> 2) ^ (site >> 1)) & 7) << 2) + (ch & 3);
+}
+__device__ __forceinline__ f4 gread4(const float* X, int site, int ch) {
+  return *reinterpret_cast<const f4*>(X + gidx(site, ch));
+}
+__device__ __forceinline__ void gwrite4(float* X, int site, int ch, f4 v) {
+  *reinterpret_cast<f4*>(X + gidx(site, ch)) = v;
+}
+__device__ __forceinline__ f4 mfma_f32(float a, float b, f4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// LDS (floats): z[256], X0..X3, o[9][N], the log-probabilities and scratch of
+// net_logprobs, the neighbour table [9][256] (bytes)
+__host__ __device__ inline size_t net_grad_lds_bytes(int N) { return (size_t)(280 + 147 * N + 9 * 64) * 4; }
+
+// One 32 -> 32 layer over the block's sites: fin(site, ch, v) takes channels ch
+// .. ch + 3 of a site.  wt[t][e]: this lane's weights of tap t, input channel
+// 8 g + e; tap t reads the site nb[flip ? 8 - t : t].
+template <class F>
+__device__ __forceinline__ void net_grad_conv(const float (&wt)[9][8], const float* X, const uint8_t* nbt, int N,
+                                              bool flip, F&& fin) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g = lane >> 4, m = lane & 15, ct = wave & 1;
+  for (int st = wave >> 1; st < (N + 15) / 16; st += 2) {
+    const int site = st * 16 + m, sc = site < N ? site : 0;
+    // one sum per row of taps: shorter chains, and less rounding than one of 288
+    f4 acc[3];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      const int nb = nbt[(flip ? 8 - t : t) * 256 + sc];
+      const f4 lo = gread4(X, nb, 8 * g), hi = gread4(X, nb, 8 * g + 4);
+      f4& x = acc[t / 3];
+      if (t % 3 == 0) x = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x = mfma_f32(wt[t][e], lo[e], x);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x = mfma_f32(wt[t][4 + e], hi[e], x);
     }
-  }
-  // dh3 -> G, then da3 = dh3 * SiLU'(a3)
-  if (act) {
-    for (int ch = 0; ch < kNetC; ++ch) {
-      float s = 0.f;
-      for (int kk = 0; kk < 9; ++kk) s = fmaf(a.P[oWh + kk * kNetC + ch], o[kk * N + i], s);
-      G[ch * N + i] = s * silu_grad(A3[ch * N + i]);
-    }
-  }
-  __syncthreads();
-  // layer 3 (input h2 = SiLU(A2)) and layer 2 (input h1 = SiLU(A1)):
-  // dW[co][ci][t] = sum_i da[co][i] h[ci][nb(i, t)], db[co] = sum_i da[co][i],
-  // dh[ci][j] = sum_{co,t} W[co][ci][t] da[co][nb(j, 8 - t)]
-  auto conv_back = [&](const float* __restrict__ Wl, int oW, int ob, const float* da, const float* ain,
-                       float* dh_out) {
-    for (int p = i; p < kNetC * 9; p += 256) {
-      const int ci = p / 9, t = p % 9;
-      float acc[kNetC];
-#pragma unroll
-      for (int co = 0; co < kNetC; ++co) acc[co] = 0.f;
-      for (int j = 0; j < N; ++j) {
-        // the site whose tap-t neighbour is read at j's position: input at nb(j, t)
-        const int x = j % g.Lx, y = j / g.Lx;
-        const int nbj = ((y + t / 3 - 1 + g.Ly) % g.Ly) * g.Lx + (x + t % 3 - 1 + g.Lx) % g.Lx;
-        const float hv = silu_f(ain[ci * N + nbj]);
-#pragma unroll
-        for (int co = 0; co < kNetC; ++co) acc[co] = fmaf(da[co * N + j], hv, acc[co]);
-      }
-#pragma unroll
-      for (int co = 0; co < kNetC; ++co) out[oW + (co * kNetC + ci) * 9 + t] = acc[co];
-    }
-    for (int co = i; co < kNetC; co += 256) {
-      float s = 0.f;
-      for (int j = 0; j < N; ++j) s += da[co * N + j];
-      out[ob + co] = s;
-    }
-    float acc[kNetC];
-#pragma unroll
-    for (int ci = 0; ci < kNetC; ++ci) acc[ci] = 0.f;
-    if (act) {
-      for (int co = 0; co < kNetC; ++co)
-#pragma unroll
-        for (int t = 0; t < 9; ++t) {
-          const float d = da[co * N + g.nb[8 - t]];
-#pragma unroll
-          for (int ci = 0; ci < kNetC; ++ci) acc[ci] = fmaf(Wl[(co * kNetC + ci) * 9 + t], d, acc[ci]);
-        }
-      // dh_out is none of the buffers read above
-#pragma unroll
-      for (int ci = 0; ci < kNetC; ++ci) dh_out[ci * N + i] = acc[ci] * silu_grad(ain[ci * N + i]);
-    }
-    __syncthreads();
-  };
-  conv_back(a.P + oW3, oW3, ob3, G, A2, A3);   // A3 is free: da2 goes there
-  conv_back(a.P + oW2, oW2, ob2, A3, A1, G);   // da1 goes to G
-  // layer 1: input z, one channel
-  for (int p = i; p < kNetC * 9; p += 256) {
-    const int co = p / 9, t = p % 9;
-    float s = 0.f;
-    for (int j = 0; j < N; ++j) {
-      const int x = j % g.Lx, y = j / g.Lx;
-      const int nbj = ((y + t / 3 - 1 + g.Ly) % g.Ly) * g.Lx + (x + t % 3 - 1 + g.Lx) % g.Lx;
-      s = fmaf(G[co * N + j], z[nbj], s);
-    }
-    out[oW1 + co * 9 + t] = s;
-  }
-  for (int co = i; co < kNetC; co += 256) {
-    float s = 0.f;
-    for (int j = 0; j < N; ++j) s += G[co * N + j];
-    out[ob1 + co] = s;
+    if (site < N) fin(site, ct * 16 + 4 * g, (acc[0] + acc[1]) + acc[2]);
   }
 }
 
-__host__ __device__ inline size_t net_grad_lds_bytes(int N) { return (size_t)(280 + 147 * N) * 4; }
+// dW += da^T h over the sites for this wave's (co tile, ci tile) and all taps;
+// db += da (co of this lane)
+__device__ __forceinline__ void net_grad_weights(const float* DA, const float* H, const uint8_t* nbt, int N, f4 (&dW)[9],
+                                                 float& db) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g = lane >> 4, m = lane & 15, co = (wave & 1) * 16 + m, ci = (wave >> 1) * 16 + m;
+  for (int s = 0; s < N; s += 4) {
+    const int site = s + g, sc = site < N ? site : 0;
+    float a = DA[gidx(sc, co)];
+    a = site < N ? a : 0.f;
+    db += a;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) dW[t] = mfma_f32(a, H[gidx(nbt[t * 256 + sc], ci)], dW[t]);
+  }
+}
 
-// Sum over samples in two fixed-order stages: slice y of S adds its share
-// of the samples, then net_reduce_kernel adds the S slices.
+__global__ void __launch_bounds__(256, 2) net_grad_kernel(NetGradArgs a) {
+  extern __shared__ __align__(16) float lds[];
+  NetGeo geo;
+  geo.Lx = a.Lx; geo.Ly = a.Ly; geo.N = a.Lx * a.Ly;
+  const int N = geo.N, i = threadIdx.x;
+  const bool act = i < N;
+  const int lane = i & 63, wave = i >> 6, g = lane >> 4, m = lane & 15;
+  float* z = lds;
+  float* X0 = z + 256;
+  float* X1 = X0 + kNetC * N;
+  float* X2 = X1 + kNetC * N;
+  float* X3 = X2 + kNetC * N;
+  float* o = X3 + kNetC * N;
+  double* lc = reinterpret_cast<double*>(o + 9 * N + (N & 1));
+  float* lk = reinterpret_cast<float*>(lc + N);
+  double* shd = reinterpret_cast<double*>(lk + 8 * N + ((8 * N) & 1));
+  float* shf = reinterpret_cast<float*>(shd + 4);
+  uint8_t* nbt = reinterpret_cast<uint8_t*>(lds + 280 + 147 * N);
+  for (int p = i; p < 9 * 256; p += 256) {
+    const int t = p / 256, s = p % 256 < N ? p % 256 : 0, x = s % a.Lx, y = s / a.Lx;
+    nbt[p] = (uint8_t)(((y + t / 3 - 1 + a.Ly) % a.Ly) * a.Lx + (x + t % 3 - 1 + a.Lx) % a.Lx);
+  }
+  const float* __restrict__ P = a.P;
+  // elementwise work: this thread's four channels of every 32nd site
+  const int ec = 4 * (i & 7), es = i >> 3;
+  // sums over the block's samples
+  f4 dW3[9], dW2[9], dW1 = {0.f, 0.f, 0.f, 0.f}, dWh = {0.f, 0.f, 0.f, 0.f};
+  float db3 = 0.f, db2 = 0.f, db1 = 0.f, dbh = 0.f;
+#pragma unroll
+  for (int t = 0; t < 9; ++t) { dW3[t] = f4{0.f, 0.f, 0.f, 0.f}; dW2[t] = f4{0.f, 0.f, 0.f, 0.f}; }
+  const int ct = wave & 1;
+  // this lane's weights of a layer (row 16 ct + m of the product), forward or transposed
+  auto weights = [&](int oW, bool tr, float (&wt)[9][8]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int co = tr ? 8 * g + e : 16 * ct + m, ci = tr ? 16 * ct + m : 8 * g + e;
+#pragma unroll
+      for (int t = 0; t < 9; ++t) wt[t][e] = P[oW + (co * kNetC + ci) * 9 + t];
+    }
+  };
+  for (int b = blockIdx.x; b < a.B; b += gridDim.x) {
+    const uint64_t* sw = a.spins + (size_t)b * a.nw;
+    __syncthreads();  // the last sample's buffers are free
+    if (act) z[i] = 1.f - 2.f * (float)spin_bit(sw, i);
+    __syncthreads();
+    // layer 1: a1 -> X0, h1 -> X1
+    for (int s = es; s < N; s += 32) {
+      f4 v;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = P[ob1 + ec + q];
+#pragma unroll
+      for (int t = 0; t < 9; ++t) {
+        const float x = z[nbt[t * 256 + s]];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = fmaf(P[oW1 + (ec + q) * 9 + t], x, v[q]);
+      }
+      gwrite4(X0, s, ec, v);
+      gwrite4(X1, s, ec, f4{silu_f(v[0]), silu_f(v[1]), silu_f(v[2]), silu_f(v[3])});
+    }
+    __syncthreads();
+    // layer 2: a2 -> X2, h2 -> X3
+    {
+      float wt[9][8];
+      weights(oW2, false, wt);
+      net_grad_conv(wt, X1, nbt, N, false, [&](int s, int ch, f4 v) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] += P[ob2 + ch + q];
+        gwrite4(X2, s, ch, v);
+        gwrite4(X3, s, ch, f4{silu_f(v[0]), silu_f(v[1]), silu_f(v[2]), silu_f(v[3])});
+      });
+    }
+    __syncthreads();
+    // layer 3: a3 -> X1
+    {
+      float wt[9][8];
+      weights(oW3, false, wt);
+      net_grad_conv(wt, X3, nbt, N, false, [&](int s, int ch, f4 v) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] += P[ob3 + ch + q];
+        gwrite4(X1, s, ch, v);
+      });
+    }
+    __syncthreads();
+    // head: o[k][site], k on the tile's rows
+    {
+      float wh[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) wh[e] = m < 9 ? P[oWh + m * kNetC + 8 * g + e] : 0.f;
+      for (int st = wave; st < (N + 15) / 16; st += 4) {
+        const int site = st * 16 + m, sc = site < N ? site : 0;
+        const f4 lo = gread4(X1, sc, 8 * g), hi = gread4(X1, sc, 8 * g + 4);
+        f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc = mfma_f32(wh[e], silu_f(e < 4 ? lo[e & 3] : hi[e & 3]), acc);
+        if (site < N)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (4 * g + q < 9) o[(4 * g + q) * N + site] = acc[q] + P[obh + 4 * g + q];
+      }
+    }
+    __syncthreads();
+    net_logprobs(o, geo, lc, lk, shd, shf);
+    const int c = a.moves[b] & 0xffff, k = a.moves[b] >> 16;
+    const double coef = -((double)a.accept_prob[b] * k - *a.baseline) / a.B;
+    // d loss / d o, written over o: channel 0 at every site, size channels at c
+    if (act) {
+      o[i] = (float)(coef * ((i == c ? 1.0 : 0.0) - exp(lc[i])));
+      for (int q = 0; q < 8; ++q)
+        o[(q + 1) * N + i] = (i == c) ? (float)(coef * ((q + 1 == k ? 1.0 : 0.0) - exp((double)lk[q * N + i]))) : 0.f;
+    }
+    __syncthreads();
+    // head: dWh[k][ch] += sum_i do[k][i] h3[ch][i] (waves 0 and 1: channel tiles)
+    if (wave < 2) {
+      for (int s = 0; s < N; s += 4) {
+        const int site = s + g, sc = site < N ? site : 0;
+        const float d = m < 9 && site < N ? o[m * N + sc] : 0.f;
+        dbh += d;
+        dWh = mfma_f32(d, silu_f(X1[gidx(sc, 16 * wave + m)]), dWh);
+      }
+    }
+    __syncthreads();
+    // da3 = (Wh^T do) SiLU'(a3) -> X1
+    for (int s = es; s < N; s += 32) {
+      f4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int q9 = 0; q9 < 9; ++q9) {
+        const float d = o[q9 * N + s];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = fmaf(P[oWh + q9 * kNetC + ec + q], d, v[q]);
+      }
+      const f4 a3 = gread4(X1, s, ec);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] *= silu_grad(a3[q]);
+      gwrite4(X1, s, ec, v);
+    }
+    __syncthreads();
+    // layer 3: dW3 from da3 and h2; da2 = (W3^T da3) SiLU'(a2) -> X2
+    net_grad_weights(X1, X3, nbt, N, dW3, db3);
+    {
+      float wt[9][8];
+      weights(oW3, true, wt);
+      net_grad_conv(wt, X1, nbt, N, true, [&](int s, int ch, f4 v) {
+        const f4 a2 = gread4(X2, s, ch);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] *= silu_grad(a2[q]);
+        gwrite4(X2, s, ch, v);
+      });
+    }
+    __syncthreads();
+    // h1 -> X3
+    for (int s = es; s < N; s += 32) {
+      const f4 v = gread4(X0, s, ec);
+      gwrite4(X3, s, ec, f4{silu_f(v[0]), silu_f(v[1]), silu_f(v[2]), silu_f(v[3])});
+    }
+    __syncthreads();
+    // layer 2: dW2 from da2 and h1; da1 = (W2^T da2) SiLU'(a1) -> X0
+    net_grad_weights(X2, X3, nbt, N, dW2, db2);
+    {
+      float wt[9][8];
+      weights(oW2, true, wt);
+      net_grad_conv(wt, X2, nbt, N, true, [&](int s, int ch, f4 v) {
+        const f4 a1 = gread4(X0, s, ch);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] *= silu_grad(a1[q]);
+        gwrite4(X0, s, ch, v);
+      });
+    }
+    __syncthreads();
+    // layer 1: dW1[co][t] += sum_i da1[co][i] z[nb(i, t)] (waves 0 and 1), taps on the tile's columns
+    if (wave < 2) {
+      for (int s = 0; s < N; s += 4) {
+        const int site = s + g, sc = site < N ? site : 0;
+        float d = X0[gidx(sc, 16 * wave + m)];
+        d = site < N ? d : 0.f;
+        db1 += d;
+        dW1 = mfma_f32(d, m < 9 ? z[nbt[m * 256 + sc]] : 0.f, dW1);
+      }
+    }
+  }
+  // the block's partial gradient: lane (g, m) holds rows 4 g + q and column m of its tiles
+  float* out = a.partial + (size_t)blockIdx.x * kNetParams;
+  db3 = group_sum(db3);
+  db2 = group_sum(db2);
+  db1 = group_sum(db1);
+  dbh = group_sum(dbh);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int co = ct * 16 + 4 * g + q, ci = (wave >> 1) * 16 + m;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      out[oW3 + (co * kNetC + ci) * 9 + t] = dW3[t][q];
+      out[oW2 + (co * kNetC + ci) * 9 + t] = dW2[t][q];
+    }
+    if (wave < 2) {
+      if (m < 9) out[oW1 + (16 * wave + 4 * g + q) * 9 + m] = dW1[q];
+      if (4 * g + q < 9) out[oWh + (4 * g + q) * kNetC + 16 * wave + m] = dWh[q];
+    }
+  }
+  if (g == 0 && wave < 2) {
+    out[ob3 + 16 * wave + m] = db3;
+    out[ob2 + 16 * wave + m] = db2;
+    out[ob1 + 16 * wave + m] = db1;
+    if (wave == 0 && m < 9) out[obh + m] = dbh;
+  }
+}
+
+// Sum over the blocks' partial gradients in two fixed-order stages: slice y of
+// S adds its share, then net_reduce_kernel adds the S slices.
 __global__ void net_reduce_slices_kernel(const float* partial, int B, int S, float* out) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x, y = blockIdx.y;
   if (p >= kNetParams) return;
