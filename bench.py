@@ -89,7 +89,7 @@ def baseline_sweep_rowsteps(pi, N, L):
 # counter figures taken on other versions of these are stale.  (The host
 # tensor-train algebra, the narrow-bond and the learned-proposal kernels
 # cannot change what the matrix-core kernels read and write.)
-KERNEL_SOURCES = ("csrc/rtt_device.hpp", "csrc/rtt_kernels.hpp", "csrc/rtt_chain.hpp", "csrc/rtt_lib.hip", "build.py")
+KERNEL_SOURCES = ("csrc/rtt_device.hpp", "csrc/rtt_kernels.hpp", "csrc/rtt_chain.hpp", "csrc/rtt_tile.hpp", "csrc/rtt_lib.hip", "build.py")
 
 
 def src_hash():

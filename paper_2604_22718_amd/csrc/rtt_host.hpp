@@ -72,6 +72,20 @@ inline size_t pass_lds_bytes(int chi, int nslot, int nw, int dtype) {
   return (size_t)wpb * (nb * nslot * rs * 4 + nb * nslot * 4 + nw * 8);
 }
 
+// Passes whose rows stay in the registers of one wave per walker: at bond 32
+// always (8x8, BF16 evaluation: 16 walkers 160 -> 147 us, 4096 472 -> 328 us);
+// at bond 64 from a pass per SIMD, where the rows-in-LDS form's four waves per
+// walker queue for the chip (8x8: 1024 walkers 316 -> 250 us, 4096 941 -> 615
+// us; below that a lone wave's chain of steps is the longer, 512 walkers 191
+// against 241 us).  passes: walkers x terms x row groups of the launch.
+inline bool pass_wave(int dtype, int chi, int nslot, long passes) {
+  return dtype != RTT_F32 && chi <= 64 && nslot <= 16 * rttk::kPassWaveTiles &&
+         (chi <= 32 || passes >= 4L * device_cus());
+}
+inline size_t pass_wave_lds(int dtype, int chi) { return rttk::pass_wave_lds(chi, dtype == RTT_FP8_E4M3 ? 1 : 2); }
+// walkers per block of a pass
+inline int pass_walkers(int chi, bool wave) { return wave ? 4 : 4 / rttk_wpw(chi); }
+
 // walkers from which a launch gives every compute unit 32 of them
 inline bool two_groups(int W) { return W >= 32 * device_cus(); }
 // FP8 cores at bond 256 with that many: the sampler's prefixes are in global memory

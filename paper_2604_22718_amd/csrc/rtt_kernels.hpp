@@ -12,6 +12,7 @@
 #include <type_traits>
 
 #include "rtt_device.hpp"
+#include "rtt_tile.hpp"
 
 namespace rttk {
 
@@ -50,6 +51,7 @@ struct PassArgs {
   const uint64_t* spins;    // [W][nw]
   float* out_vec;           // [T][ng][W][nslot][CHI]
   int32_t* out_exp;         // [T][ng][W][nslot]
+  int wave;                 // batched passes: items are for the wave-resident form
 };
 
 // ----------------------------------------------------------------------------
@@ -346,6 +348,264 @@ __device__ __forceinline__ void pass_body_wide(const PassArgs& a, int bx, int ty
   }
 }
 
+// ----------------------------------------------------------------------------
+// Wave-resident flip-ratio pass (BF16 and FP8 cores up to bond 64): one wave
+// per walker, every row in its registers from the boundary to the cut.  Every
+// walker needs one slice of a site for its rows and, where the site's spin is
+// of its group, the other for the odd row, so a block stages both for its four
+// walkers, a site ahead, in two halves of LDS: one barrier per step, and a
+// quarter of the slice traffic.  A row tile is multiplied chunk by chunk, hi
+// part then lo part, as in pass_body (the results are the same bits), split
+// and kept; the odd row is the column of its tile's product with the other
+// slice, moved to its slot.
+// Bound by issue: 16 matrix ops and 64 vector ops (split, selection) per row
+// tile at bond 64, one more tile per step for the odd row.  8x8 BF16 bond 64,
+// 4096 walkers, one pass: 446 us with the rows in LDS and four waves per
+// walker, 280 us here (matrix ops alone 103 us).  With slices in registers
+// instead of LDS the rows spilled (350 us), and at one wave per SIMD vector
+// and matrix ops do not overlap (390 us).
+// Up to kPassWaveTiles row tiles, which two waves per SIMD can hold.
+constexpr int kPassWaveTiles = 5;
+template <class D, int CHI>
+constexpr bool pass_wave_bond() { return !D::kF32 && CHI <= 64; }
+constexpr size_t pass_wave_lds(int chi, int elem_bytes) { return (size_t)4 * chi * chi * elem_bytes; }
+
+template <int A, int B, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (A < B) {
+    f(std::integral_constant<int, A>{});
+    static_for<A + 1, B>(f);
+  }
+}
+
+template <class D, int CHI, int NTM>
+__device__ __forceinline__ void pass_body_wave(const PassArgs& a, int bx, int ty) {
+  using E = typename D::elem;
+  using Op = TileOp<D, CHI>;
+  using Fr = Frag<E, CHI / 4>;
+  constexpr int NV = CHI / 16, KPL = CHI / 4, NCH = CHI / 32;
+  constexpr int SLICE = CHI * CHI * (int)sizeof(E), TILE = 64 * KPL * (int)sizeof(E);
+  constexpr int NS = (2 * SLICE + 4095) / 4096;  // 16-byte words of a site that a thread stages
+  extern __shared__ __align__(16) float lds[];
+  char* buf = reinterpret_cast<char*>(lds);  // [2][slice of bit 0, slice of bit 1]
+  const int tid = threadIdx.x, lane = tid & 63, m = lane & 15;
+  const int w_raw = bx * 4 + __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int w = min(w_raw, a.W - 1), term = ty / a.ng, grp = ty % a.ng;
+  const char* cores = static_cast<const char*>(a.cores) + (size_t)term * a.L * 2 * SLICE;
+  const int4* sched = a.sched + uniform_load(&a.gsteps[grp].x, 0);
+  const int n = uniform_load(&a.gsteps[grp].y, 0);
+  const uint64_t* spins = a.spins + (size_t)w * a.nw;
+  u32x4 r[NTM][NV];
+  int ex[NTM];
+#pragma unroll
+  for (int t = 0; t < NTM; ++t) {
+    ex[t] = 0;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) r[t][v] = u32x4{0, 0, 0, 0};
+  }
+  r[0][0][0] = lane == 0 ? Op::kUnit : 0u;  // boundary vector e_0 in the base slot
+  // A step's entry is read three steps ahead and the walker's spin two; both
+  // slices of the next site are on their way to LDS during a whole step.
+  struct Step { int k, q, nact, odd, bit, cexp; };
+  auto entry = [&](int s, Step& st) {
+    const int* e = &sched[min(s, n - 1)].x;
+    st.k = uniform_load(e, 0);
+    st.q = uniform_load(e, 1);
+    st.nact = uniform_load(e, 2);
+    st.odd = uniform_load(e, 3);
+  };
+  auto spin = [&](Step& st) {
+    st.bit = (int)((uniform_load(spins, st.q >> 6) >> (st.q & 63)) & 1ull);
+    st.cexp = a.core_exp ? uniform_load(a.core_exp, (long long)term * a.L + st.k) : 0;
+  };
+  u32x4 stage[NS];
+  auto fetch = [&](int k) {
+    typedef const __attribute__((address_space(1))) u32x4* gvec;
+    const gvec p = (gvec)(cores + (size_t)k * 2 * SLICE);
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+      if (16 * (256 * i + tid) < 2 * SLICE) stage[i] = p[256 * i + tid];
+  };
+  auto put = [&](int half) {
+    u32x4* p = reinterpret_cast<u32x4*>(buf + half * 2 * SLICE);
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+      if (16 * (256 * i + tid) < 2 * SLICE) p[256 * i + tid] = stage[i];
+  };
+  auto read = [&](Fr& f, const char* p) {
+    if constexpr (Fr::NW % 4 == 0) {
+#pragma unroll
+      for (int i = 0; i < Fr::NW / 4; ++i) {
+        const u32x4 v = reinterpret_cast<const u32x4*>(p)[64 * i + lane];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f.w[4 * i + j] = v[j];
+      }
+    } else {
+      const uint2 v = reinterpret_cast<const uint2*>(p)[lane];
+      f.w[0] = v.x;
+      f.w[1] = v.y;
+    }
+  };
+  // output tile t of the vectors in times a slice, renormalised by sc, as words
+  auto tile = [&](auto rnc, const Fr& f, const u32x4(&in)[NV], float sc, u32x4(&out)[NV], int t) {
+    constexpr bool RN = decltype(rnc)::value;
+    f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      typename Op::Operand x;
+#pragma unroll
+      for (int q = 0; q < Op::kPieces; ++q) Op::decode(f, c, q, x);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) acc = Op::op(x, in, c, h, acc);
+    }
+    typename Op::Post ps;
+#pragma unroll
+    for (int st = 0; st < Op::kStages; ++st) Op::template post<RN, NV>(st, ps, false, acc, acc, sc, out, t);
+  };
+  Step cur = {0, 0, 0, -1, 0, 0}, nxt = cur, n2 = cur;
+  if (n > 0) {
+    entry(0, cur);
+    entry(1, nxt);
+    entry(2, n2);
+    spin(cur);
+    spin(nxt);
+    fetch(cur.k);
+    put(0);
+    lds_barrier();
+  }
+  auto step = [&](auto ntc, auto rnc, int half) {
+    constexpr int NT = decltype(ntc)::value;
+    constexpr bool RN = decltype(rnc)::value;
+    const int oin = cur.odd >= 0 ? (cur.odd & 0xffff) : -1, oout = cur.odd >> 16;
+    const char* own = buf + (half * 2 + cur.bit) * SLICE;
+    const char* other = buf + (half * 2 + (cur.bit ^ 1)) * SLICE;
+    // scale factor of a tile's product and its columns' exponents after the step
+    auto rescale = [&](const u32x4(&x)[NV], int& e) {
+      float sc = 1.f;
+      if constexpr (RN) {
+        const int me = Op::row_exp(x);
+        sc = __builtin_amdgcn_ldexpf(1.f, -me);  // exact power of two
+        e += me;
+      }
+      e += cur.cexp;
+      return sc;
+    };
+    fetch(nxt.k);
+    hold_loads();
+    u32x4 ow[NV];
+    int oe = ex[0];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) ow[v] = r[0][v];
+    if (oin >= 0) {
+      u32x4 x[NV];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) x[v] = r[0][v];
+#pragma unroll
+      for (int t = 1; t < NT; ++t)
+        if (t == (oin >> 4)) {
+          oe = ex[t];
+#pragma unroll
+          for (int v = 0; v < NV; ++v) x[v] = r[t][v];
+        }
+      const float sc = rescale(x, oe);
+#pragma unroll
+      for (int t = 0; t < NV; ++t) {
+        Fr f;
+        read(f, other + t * TILE);
+        tile(rnc, f, x, sc, ow, t);
+      }
+      if (oin == 0 && oout != 0) {  // spawned from the base row: column 0 to every column
+        oe = __builtin_amdgcn_update_dpp(0, oe, 0x150, 0xf, 0xf, true);
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            ow[v][i] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ow[v][i], 0x150, 0xf, 0xf, true);
+      }
+    }
+    Fr F[NV];
+#pragma unroll
+    for (int t = 0; t < NV; ++t) read(F[t], own + t * TILE);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const float sc = rescale(r[t], ex[t]);
+      u32x4 o[NV];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) tile(rnc, F[v], r[t], sc, o, v);
+#pragma unroll
+      for (int v = 0; v < NV; ++v) r[t][v] = o[v];
+    }
+    if (oin >= 0) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const bool mine = 16 * t + m == oout;
+        ex[t] = mine ? oe : ex[t];
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) r[t][v][i] = mine ? ow[v][i] : r[t][v][i];
+      }
+    }
+    put(half ^ 1);
+    lds_barrier();
+  };
+  // as many tiles as a step has rows for (their number only grows)
+  int s = 0;
+  static_for<1, NTM + 1>([&](auto ntc) {
+    constexpr int NT = decltype(ntc)::value;
+    while (s < n && (NT == NTM || cur.nact <= 16 * NT)) {
+      Step n3 = n2;
+      entry(s + 3, n3);
+      spin(n2);
+      if (s % kRenormEvery == 0) step(ntc, std::true_type{}, s & 1);
+      else step(ntc, std::false_type{}, s & 1);
+      cur = nxt;
+      nxt = n2;
+      n2 = n3;
+      ++s;
+    }
+  });
+  if (w_raw >= a.W) return;  // no barrier below
+  const int g = lane >> 4;
+  float* ov = a.out_vec + ((size_t)ty * a.W + w) * a.nslot * CHI;
+  int32_t* oe_out = a.out_exp + ((size_t)ty * a.W + w) * a.nslot;
+#pragma unroll
+  for (int t = 0; t < NTM; ++t) {
+    if (16 * t >= a.nslot) break;
+    float* d = ov + (size_t)(16 * t + m) * CHI + g * KPL;
+#pragma unroll
+    for (int c = 0; c < NV / 2; ++c)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {  // elements 8 c + 4 q .. + 3
+        const uint32_t h0 = r[t][2 * c][2 * q], h1 = r[t][2 * c][2 * q + 1];
+        const uint32_t l0 = r[t][2 * c + 1][2 * q], l1 = r[t][2 * c + 1][2 * q + 1];
+        *reinterpret_cast<float4*>(d + 8 * c + 4 * q) = make_float4(
+            __uint_as_float(h0 << 16) + __uint_as_float(l0 << 16),
+            __uint_as_float(h0 & 0xffff0000u) + __uint_as_float(l0 & 0xffff0000u),
+            __uint_as_float(h1 << 16) + __uint_as_float(l1 << 16),
+            __uint_as_float(h1 & 0xffff0000u) + __uint_as_float(l1 & 0xffff0000u));
+      }
+    if (g == 0) oe_out[16 * t + m] = ex[t];
+  }
+}
+
+// the body for the schedule's row tiles
+template <class D, int CHI>
+__device__ __forceinline__ void pass_wave_any(const PassArgs& a, int bx, int ty) {
+  switch (a.nslot / 16) {
+    case 1: pass_body_wave<D, CHI, 1>(a, bx, ty); break;
+    case 2: pass_body_wave<D, CHI, 2>(a, bx, ty); break;
+    case 3: pass_body_wave<D, CHI, 3>(a, bx, ty); break;
+    case 4: pass_body_wave<D, CHI, 4>(a, bx, ty); break;
+    default: pass_body_wave<D, CHI, 5>(a, bx, ty); break;
+  }
+}
+
+template <class D, int CHI>
+__global__ void __launch_bounds__(256, 2) pass_wave_kernel(PassArgs a) {
+  pass_wave_any<D, CHI>(a, blockIdx.x, blockIdx.y);
+}
+
 template <class D, int CHI>
 __device__ __forceinline__ void pass_body(const PassArgs& a, int bx, int ty) {
   if constexpr (pass_wide_form<D, CHI>()) {
@@ -603,7 +863,7 @@ __device__ __forceinline__ int next_item(int* counter, int* s_item) {
 }
 
 template <class D, int CHI>
-__global__ void __launch_bounds__(256, (pass_min_blocks<D, CHI>())) pass_persistent(const PassArgs* descs, const int4* items,
+__global__ void __launch_bounds__(256, (pass_wave_bond<D, CHI>() ? 2 : pass_min_blocks<D, CHI>())) pass_persistent(const PassArgs* descs, const int4* items,
                                                        int n_items, int* counter) {
   __shared__ int s_item;
   for (;;) {
@@ -611,7 +871,12 @@ __global__ void __launch_bounds__(256, (pass_min_blocks<D, CHI>())) pass_persist
     if (it >= n_items) break;
     const int4 w = items[it];
     const PassArgs a = descs[w.x];
-    pass_body<D, CHI>(a, w.y, w.z);
+    if constexpr (pass_wave_bond<D, CHI>()) {
+      if (a.wave) pass_wave_any<D, CHI>(a, w.y, w.z);
+      else pass_body<D, CHI>(a, w.y, w.z);
+    } else {
+      pass_body<D, CHI>(a, w.y, w.z);
+    }
     __syncthreads();
   }
 }

@@ -1545,7 +1545,11 @@ static rtt_status rtt_batch_create_impl(int32_t n, const rtt_t* rtts, const rtt_
     }
     std::sort(order.begin(), order.end(), [](auto& x, auto& y) { return x.first > y.first; });
     c.members.clear();
-    for (auto& o : order) c.members.push_back(o.second);
+    long passes = 0;  // of one launch: every member, both directions
+    for (auto& o : order) {
+      c.members.push_back(o.second);
+      passes += 2L * b->W[o.second] * b->rtts[o.second]->T * b->rtts[o.second]->sched.ng;
+    }
     for (int mi = 0; mi < (int)c.members.size(); ++mi) {
       const int i = c.members[mi];
       rtt_s* h = b->rtts[i];
@@ -1563,16 +1567,18 @@ static rtt_status rtt_batch_create_impl(int32_t n, const rtt_t* rtts, const rtt_
       pa.ng = h->sched.ng;
       pa.cores = h->d_fwd; pa.sched = h->d_sf; pa.gsteps = h->d_fgs;
       pa.out_vec = ws_u(i); pa.out_exp = ws_ue(i);
+      const bool wave = pass_wave(c.dtype, c.chi, h->sched.nslot, passes);
+      pa.wave = wave;
       c.pass.push_back(pa);
       pa.cores = h->d_bwd; pa.sched = h->d_sb; pa.gsteps = h->d_bgs;
       pa.out_vec = ws_v(i); pa.out_exp = ws_ve(i);
       c.pass.push_back(pa);
-      c.pass_lds = std::max(c.pass_lds, pass_lds_bytes(c.chi, h->sched.nslot, h->nw, h->dtype));
+      c.pass_lds = std::max(c.pass_lds, wave ? pass_wave_lds(c.dtype, c.chi) : pass_lds_bytes(c.chi, h->sched.nslot, h->nw, h->dtype));
       // sweep cost ~ (L + sum_j (L - first_j)) row-steps per walker tile
       double sweep_rows = h->L;
       for (int j = 0; j < h->N; ++j) if (h->first[j] >= 0) sweep_rows += h->L - h->first[j];
       c.chain_cost += sweep_rows * h->T * ((W + 15) / 16) * 16 * (double)c.chi * c.chi;
-      const int wpb = 4 / rttk_wpw(c.chi);
+      const int wpb = pass_walkers(c.chi, wave);
       c.pass_cost += (double)h->sched.cost * 16 * h->T * W * (double)c.chi * c.chi;
 
       for (int dir = 0; dir < 2; ++dir)

@@ -16,12 +16,18 @@ constexpr int kDtype = rtt_host::kDtypeOf<Cores>;
 
 template <class D, int CHI>
 rtt_status launch_pass(const rttk::PassArgs& a, int T, hipStream_t s) {
-  constexpr int WPW = rttk::Geo<CHI>::WPW;
-  constexpr int WPB = 4 / WPW;
+  const bool wave = pass_wave(kDtype, CHI, a.nslot, (long)a.W * T);
+  const int wpb = pass_walkers(CHI, wave);
+  dim3 grid((a.W + wpb - 1) / wpb, T);
+  if constexpr (rttk::pass_wave_bond<D, CHI>())
+    if (wave) {
+      hipLaunchKernelGGL((rttk::pass_wave_kernel<D, CHI>), grid, dim3(256), rtt_host::pass_wave_lds(kDtype, CHI), s, a);
+      HIPX(hipGetLastError());
+      return RTT_OK;
+    }
   const size_t lds = pass_lds_bytes(CHI, a.nslot, a.nw, kDtype);
   auto kfn = rttk::pass_kernel<D, CHI>;
   HIPX(hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  dim3 grid((a.W + WPB - 1) / WPB, T);
   hipLaunchKernelGGL(kfn, grid, dim3(256), lds, s, a);
   HIPX(hipGetLastError());
   return RTT_OK;
