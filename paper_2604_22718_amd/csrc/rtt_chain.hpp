@@ -225,7 +225,7 @@ __device__ __forceinline__ void samp_body(const ChainArgs& a, int bx, uint64_t s
       gchar q = p + SLICE;
       asm("" : "+s"(p));
       asm("" : "+s"(q));
-      load_frag2<E, KPL>(f, p + mt * TILE % WIN, q + mt * TILE % WIN, lane);
+      load_frag2<E, KPL, CG == 1>(f, p + mt * TILE % WIN, q + mt * TILE % WIN, lane);
     };
     if (n > 0) {
 #pragma unroll

@@ -863,8 +863,8 @@ __device__ __forceinline__ int next_item(int* counter, int* s_item) {
 }
 
 template <class D, int CHI>
-__global__ void __launch_bounds__(256, (pass_wave_bond<D, CHI>() ? 2 : pass_min_blocks<D, CHI>())) pass_persistent(const PassArgs* descs, const int4* items,
-                                                       int n_items, int* counter) {
+__global__ void __launch_bounds__(256, (pass_wave_bond<D, CHI>() ? 2 : pass_min_blocks<D, CHI>()))
+    pass_persistent(const PassArgs* descs, const int4* items, int n_items, int* counter) {
   __shared__ int s_item;
   for (;;) {
     const int it = next_item(counter, &s_item);
