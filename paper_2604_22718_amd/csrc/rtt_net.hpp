@@ -449,7 +449,7 @@ struct NetGradArgs {
 // by (site / 2) % 8 so that 16 consecutive sites read one chunk conflict-free.
 // Buffers: X0 a1 -> da1; X1 h1 -> a3 -> da3; X2 a2 -> da2; X3 h2 -> h1.
 // Matrix ops of 4096 samples at 10x10 take 330 us of all 1024 SIMDs; measured
-// 0.94 ms (one thread per site or weight, a gradient per sample: 3.5 ms with
+// 0.99 ms (one thread per site or weight, a gradient per sample: 3.5 ms with
 // the sum over samples), the rest being layer weights, LDS reads and barriers.
 __device__ __forceinline__ int gidx(int site, int ch) {
   return site * kNetC + ((((ch >> 2) ^ (site >> 1)) & 7) << 2) + (ch & 3);
@@ -496,19 +496,27 @@ __device__ __forceinline__ void net_grad_conv(const float (&wt)[9][8], const flo
 }
 
 // dW += da^T h over the sites for this wave's (co tile, ci tile) and all taps;
-// db += da (co of this lane)
+// db += da (co of this lane).  A sample is summed by itself and then added: a
+// chain over all of a block's samples would round more than a sum per sample.
 __device__ __forceinline__ void net_grad_weights(const float* DA, const float* H, const uint8_t* nbt, int N, f4 (&dW)[9],
                                                  float& db) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, m = lane & 15, co = (wave & 1) * 16 + m, ci = (wave >> 1) * 16 + m;
+  f4 w[9];
+  float b = 0.f;
+#pragma unroll
+  for (int t = 0; t < 9; ++t) w[t] = f4{0.f, 0.f, 0.f, 0.f};
   for (int s = 0; s < N; s += 4) {
     const int site = s + g, sc = site < N ? site : 0;
     float a = DA[gidx(sc, co)];
     a = site < N ? a : 0.f;
-    db += a;
+    b += a;
 #pragma unroll
-    for (int t = 0; t < 9; ++t) dW[t] = mfma_f32(a, H[gidx(nbt[t * 256 + sc], ci)], dW[t]);
+    for (int t = 0; t < 9; ++t) w[t] = mfma_f32(a, H[gidx(nbt[t * 256 + sc], ci)], w[t]);
   }
+  db += b;
+#pragma unroll
+  for (int t = 0; t < 9; ++t) dW[t] += w[t];
 }
 
 __global__ void __launch_bounds__(256, 2) net_grad_kernel(NetGradArgs a) {
@@ -624,12 +632,16 @@ __global__ void __launch_bounds__(256, 2) net_grad_kernel(NetGradArgs a) {
     __syncthreads();
     // head: dWh[k][ch] += sum_i do[k][i] h3[ch][i] (waves 0 and 1: channel tiles)
     if (wave < 2) {
+      f4 w = {0.f, 0.f, 0.f, 0.f};
+      float bsum = 0.f;
       for (int s = 0; s < N; s += 4) {
         const int site = s + g, sc = site < N ? site : 0;
         const float d = m < 9 && site < N ? o[m * N + sc] : 0.f;
-        dbh += d;
-        dWh = mfma_f32(d, silu_f(X1[gidx(sc, 16 * wave + m)]), dWh);
+        bsum += d;
+        w = mfma_f32(d, silu_f(X1[gidx(sc, 16 * wave + m)]), w);
       }
+      dbh += bsum;
+      dWh += w;
     }
     __syncthreads();
     // da3 = (Wh^T do) SiLU'(a3) -> X1
@@ -681,13 +693,17 @@ __global__ void __launch_bounds__(256, 2) net_grad_kernel(NetGradArgs a) {
     __syncthreads();
     // layer 1: dW1[co][t] += sum_i da1[co][i] z[nb(i, t)] (waves 0 and 1), taps on the tile's columns
     if (wave < 2) {
+      f4 w = {0.f, 0.f, 0.f, 0.f};
+      float bsum = 0.f;
       for (int s = 0; s < N; s += 4) {
         const int site = s + g, sc = site < N ? site : 0;
         float d = X0[gidx(sc, 16 * wave + m)];
         d = site < N ? d : 0.f;
-        db1 += d;
-        dW1 = mfma_f32(d, m < 9 ? z[nbt[m * 256 + sc]] : 0.f, dW1);
+        bsum += d;
+        w = mfma_f32(d, m < 9 ? z[nbt[m * 256 + sc]] : 0.f, w);
       }
+      db1 += bsum;
+      dW1 += w;
     }
   }
   // the block's partial gradient: lane (g, m) holds rows 4 g + q and column m of its tiles
