@@ -66,12 +66,13 @@ struct SampLayout {
                                  bool p_lds) {
     const int nb = 16 * cg, row = chi * 64 * cg;
     const int nx = sw > 1 ? 4 : tw;
-    const int tail = (2 * T + tw) * nb * 4 + T * sw * nb * 8 + kUAhead * nb * 8 + nb * (LW + nw) * 8 + 64;
-    split = !p_lds || (2 * T + nx) * row + tail <= kLds;
+    const int cks = 2 * nck * T;  // checkpoint vectors, saved and candidate
+    const int tail = (2 * T + tw + cks) * nb * 4 + T * sw * nb * 8 + kUAhead * nb * 8 + nb * (LW + nw) * 8 + 64;
+    split = !p_lds || (2 * T + nx + (ck_lds ? cks : 0)) * row + tail <= kLds;
     pb = 0;
     xb = p_lds ? (split ? 2 : 1) * T * row : 0;
     ck = xb + nx * row;
-    vec_end = ck + (ck_lds ? 2 * nck * T * row : 0);
+    vec_end = ck + (ck_lds ? cks * row : 0);
     fval = vec_end;                     // double [T][sw][nb] partial dot products
     ub = fval + T * sw * nb * 8;        // double [kUAhead][nb] uniforms of the next proposals
     pm = ub + kUAhead * nb * 8;         // uint64 [nb][LW] position bits
@@ -80,7 +81,7 @@ struct SampLayout {
     ec = ep + T * nb * 4;               // int [tw][nb] column exponents
     fexp = ec + tw * nb * 4;            // int [T][nb] amplitude exponents
     cke = fexp + T * nb * 4;            // int [2][nck][T][nb] checkpoint exponents
-    total = cke + 2 * nck * T * nb * 4;
+    total = cke + cks * nb * 4;
   }
   static constexpr int kLds = 160 * 1024;
   static constexpr int kUAhead = 16;

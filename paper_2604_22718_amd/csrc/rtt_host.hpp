@@ -35,8 +35,8 @@ inline int device_cus() {
 // Bytes that seven FP32 vectors per term (or, `seq`, one per term and five
 // shared), nck column checkpoints with as many candidates, and a block's
 // small state take: the rule by which states are accepted and by which the
-// number of checkpoints follows.  The kernels need less (SampLayout), but
-// the checkpoints decide where the rows and columns of a proposal meet and
+// number of checkpoints follows.  Blocks of 16 walkers never need more
+// (SampLayout), blocks of 32 can, and the checkpoints decide where the rows and columns of a proposal meet and
 // with it the last bits of its amplitude, so the rule is part of what a
 // seeded chain reproduces.
 struct CheckpointRule {
@@ -86,12 +86,6 @@ inline size_t pass_wave_lds(int dtype, int chi) { return rttk::pass_wave_lds(chi
 // walkers per block of a pass
 inline int pass_walkers(int chi, bool wave) { return wave ? 4 : 4 / rttk_wpw(chi); }
 
-// walkers from which a launch gives every compute unit 32 of them
-inline bool two_groups(int W) { return W >= 32 * device_cus(); }
-// FP8 cores at bond 256 with that many: the sampler's prefixes are in global memory
-inline bool chain_global_prefix(int dtype, int chi, int W) {
-  return dtype == RTT_FP8_E4M3 && chi == 256 && two_groups(W);
-}
 // Sampler tile of a class: 16 walkers per block, or 32 (two column groups
 // sharing every core fragment) at the bonds where that kernel fits in
 // registers (at 64 and 256 the second group's operands spill).
@@ -120,6 +114,8 @@ struct ChainLaunch {
   rtt_status (*batch)(int chi, const BatchLaunch& b, bool prepare, hipStream_t s);
   // LDS of a persistent sampler block (one term at a time, no checkpoints)
   size_t (*batch_lds)(int chi, int T, int L, int nw, int cg);
+  // whether a launch keeps its prefixes in global memory (pg), if given any
+  bool (*global_prefix)(int chi, const rttk::ChainArgs& a);
 };
 const PassLaunch* pass_DF32();
 const PassLaunch* pass_DBF16();

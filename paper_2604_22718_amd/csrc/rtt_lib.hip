@@ -995,6 +995,12 @@ static rtt_status chain_common(rtt_t h, int32_t W, uint64_t* spins, double* loga
   ca.T = h->T; ca.L = h->L; ca.N = h->N; ca.nw = h->nw; ca.LW = (h->L + 63) / 64; ca.W = W;
   ca.spins = spins; ca.logabs = logabs; ca.sign = sign; ca.accepts = accepts; ca.status = status;
   ca.seed = seed; ca.rstream = rstream; ca.sweep0 = sweep0; ca.n_sweeps = n_sweeps; ca.mode = mode;
+  // the lowest bond a proposal's columns can start from: one past the
+  // smallest last position over the spins
+  int lo = h->L;
+  for (int j = 0; j < h->N; ++j)
+    if (h->last[j] >= 0) lo = std::min(lo, h->last[j] + 1);
+  ca.ck_first = h->chain_ck ? lo : h->L;
   // FP8 cores at bond 256: room for 8 column checkpoints per 16 walkers of a
   // combination in global memory, grown in stream order (8 checkpoints keep
   // 0.72 of the dependent steps of contracting every proposal's columns from
@@ -1004,29 +1010,20 @@ static rtt_status chain_common(rtt_t h, int32_t W, uint64_t* spins, double* loga
   ca.ck_cap = 0;
   ca.pg = nullptr;
   if (mode == 1 && h->chi == 256 && h->dtype == RTT_FP8_E4M3) {
-    const int cap = 8;
     const bool seq = CheckpointRule(h->chi, h->T, (h->L + 63) / 64, h->nw, 0, h->N).seq;
     const size_t vec = (size_t)(W + 31) / 32 * 32 * h->T * h->chi * 4;  // a vector of every walker and term
-    const size_t ck = h->chain_ck && seq ? 2 * cap * vec : 0;
-    const size_t need = ck + (chain_global_prefix(h->dtype, h->chi, W) ? 2 * vec : 0);
+    ca.ck_cap = h->chain_ck && seq ? 8 : 0;
+    const size_t ck = 2 * ca.ck_cap * vec;
+    const size_t need = ck + (chain_launch(h->dtype)->global_prefix(h->chi, ca) ? 2 * vec : 0);
     if (need > h->ck_bytes) {
       h->ck_bytes = 0;
-      rtt_status st = grow_async((void**)&h->d_ck, need, (hipStream_t)stream);
+      rtt_status st = grow_async(&h->d_ck, need, (hipStream_t)stream);
       if (st != RTT_OK) return st;
       h->ck_bytes = need;
     }
-    if (ck) {
-      ca.ckg = h->d_ck;
-      ca.ck_cap = cap;
-    }
+    if (ck) ca.ckg = h->d_ck;
     if (need > ck) ca.pg = static_cast<char*>(h->d_ck) + ck;
   }
-  // the lowest bond a proposal's columns can start from: one past the
-  // smallest last position over the spins
-  int lo = h->L;
-  for (int j = 0; j < h->N; ++j)
-    if (h->last[j] >= 0) lo = std::min(lo, h->last[j] + 1);
-  ca.ck_first = h->chain_ck ? lo : h->L;
   return chain_launch(h->dtype)->run(h->chi, ca, (hipStream_t)stream);
 }
 
