@@ -55,7 +55,8 @@ inline bool two_groups(int W) { return W >= 32 * device_cus(); }
 // Bonds 128 and (FP8) 256 with enough walkers to give every CU a block of 32
 // run two column groups per block: each core fragment serves 32 walkers and
 // is decoded once for them (9x9, two FP8 terms, 8192 walkers: 80.6 ms a sweep
-// with 16 walkers per block before, 48.8 with 32).
+// with 16 walkers per block before, 48.8 with 32).  A block of 32 takes more
+// LDS than the 16 walkers a state is accepted by: very long trains keep 16.
 // Up to bond 64, where one wave carries a whole vector, two terms of a
 // combination advance side by side.
 struct ChainShape {
@@ -69,7 +70,7 @@ ChainShape chain_shape(const rttk::ChainArgs& a) {
   ChainShape s{1, 1, false, 0};
   if constexpr (CHI == 128 || kGlobal) {
     s.lds = samp_layout<D, CHI>(a, 2, 1, !kGlobal, !kGlobal).total;
-    if (two_groups(a.W) && (kGlobal || s.lds <= (int)kLdsLimit)) {
+    if (two_groups(a.W) && s.lds <= (int)kLdsLimit) {
       s.cg = 2;
       s.p_global = kGlobal;
       return s;

@@ -1,0 +1,39 @@
+"""FP8 cores at bond 256 with 32 walkers for every compute unit, where a block
+of 32 walkers keeps its prefixes in global memory: a train whose state fits 16
+walkers per block but not 32."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2604_22718_amd import workloads as wl
+from test_gpu_sampler_layouts import chain
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def R():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_22718_amd import rtt
+    return rtt
+
+
+def many_walkers():
+    return 32 * torch.cuda.get_device_properties(0).multi_processor_count + 21
+
+
+def test_train_past_a_block_of_32(R):
+    N, L = 1024, 5890   # 93 words of positions and 16 of spins: one more than 32 walkers leave room for
+    print(f"[case] fp8 bond 256 N={N} L={L}", flush=True)
+    pi = np.arange(L, dtype=np.int32) % 6   # the other spins are read by no position
+    bond = np.full(L + 1, 2, dtype=np.int32)
+    bond[[0, L]], bond[L // 3] = 1, 160
+    psi = R.RTT.create(N, pi, wl.gaussian_cores(bond, 700, std=0.7), "fp8")
+    bits = wl.random_spins(many_walkers(), N, 701)
+    few = bits[:53]
+    la, sg = psi.amplitudes(R.spins_to_device(wl.pack_spins(bits)))
+    lf, sf = psi.amplitudes(R.spins_to_device(wl.pack_spins(few)))
+    assert torch.equal(la[:53], lf) and torch.equal(sg[:53], sf) and bool(torch.isfinite(la).all())
+    for a, b in zip(chain(R, psi, bits, 1, 1), chain(R, psi, few, 1, 1)):
+        assert torch.equal(a[:53], b)
