@@ -28,8 +28,12 @@ template <class D, int CHI>
 rtt_status launch_chain(const rttk::ChainArgs& a0, hipStream_t s) {
   rttk::ChainArgs a = a0;
   chain_checkpoints(a, CHI);
-  const ChainShape sh = chain_shape<D, CHI>(a);
+  ChainShape sh = chain_shape<D, CHI>(a);
   if constexpr (CHI == 256 && std::is_same<D, rttk::DFP8>::value) {
+    if (sh.cg == 2 && !a.pg && a.mode == 1) {  // no memory for the prefixes: blocks of 16
+      sh.cg = 1;
+      sh.lds = samp_layout<D, CHI>(a, 1, 1, false, true).total;
+    }
     if (sh.cg == 2) return launch_chain_as<D, CHI, 2, 1, true, true, true>(a, sh.lds, s);
     return launch_chain_as<D, CHI, 1, 1, true, true, false>(a, sh.lds, s);
   } else if constexpr (CHI >= 128) {

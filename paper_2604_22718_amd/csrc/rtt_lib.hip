@@ -1014,10 +1014,24 @@ static rtt_status chain_common(rtt_t h, int32_t W, uint64_t* spins, double* loga
     const size_t vec = (size_t)(W + 31) / 32 * 32 * h->T * h->chi * 4;  // a vector of every walker and term
     ca.ck_cap = h->chain_ck && seq ? 8 : 0;
     const size_t ck = 2 * ca.ck_cap * vec;
-    const size_t need = ck + (chain_launch(h->dtype)->global_prefix(h->chi, ca) ? 2 * vec : 0);
+    size_t need = ck + (chain_launch(h->dtype)->global_prefix(h->chi, ca) ? 2 * vec : 0);
+    // The prefixes can stay in LDS, with blocks of 16 and the same results:
+    // they are not allocated inside a capture, whose memory is the graph's,
+    // and are done without where there is no room for them.
+    if (need > ck && need > h->ck_bytes) {
+      hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+      HIPX(hipStreamIsCapturing((hipStream_t)stream, &cap));
+      if (cap != hipStreamCaptureStatusNone) need = ck;
+    }
     if (need > h->ck_bytes) {
       h->ck_bytes = 0;
       rtt_status st = grow_async(&h->d_ck, need, (hipStream_t)stream);
+      if (st == RTT_E_OOM && need > ck) {
+        (void)hipGetLastError();
+        g_err.clear();
+        need = ck;
+        st = ck ? grow_async(&h->d_ck, ck, (hipStream_t)stream) : RTT_OK;
+      }
       if (st != RTT_OK) return st;
       h->ck_bytes = need;
     }

@@ -1,12 +1,13 @@
 """FP8 cores at bond 256 with 32 walkers for every compute unit, where a block
 of 32 walkers keeps its prefixes in global memory: a train whose state fits 16
-walkers per block but not 32."""
+walkers per block but not 32, and a first sweep inside a stream capture,
+which may not allocate for them."""
 import numpy as np
 import pytest
 import torch
 
 from paper_2604_22718_amd import workloads as wl
-from test_gpu_sampler_layouts import chain
+from test_gpu_sampler_layouts import chain, make
 
 pytestmark = pytest.mark.gpu
 
@@ -37,3 +38,27 @@ def test_train_past_a_block_of_32(R):
     assert torch.equal(la[:53], lf) and torch.equal(sg[:53], sf) and bool(torch.isfinite(la).all())
     for a, b in zip(chain(R, psi, bits, 1, 1), chain(R, psi, few, 1, 1)):
         assert torch.equal(a[:53], b)
+
+
+def test_first_sweep_inside_a_capture(R):
+    print("[case] fp8 bond 256, first sweep captured", flush=True)
+    N, T = 5, 1
+    psi, ref = (make(R, N, 2, 256, "fp8", T, 800) for _ in range(2))
+    words = wl.pack_spins(wl.random_spins(many_walkers(), N, 801))
+    spins, want = R.spins_to_device(words), R.spins_to_device(words)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        psi.sweep(spins, seed=5, n_sweeps=1)
+    for _ in range(3):
+        graph.replay()
+        ref.sweep(want, seed=5, n_sweeps=1)
+        torch.cuda.synchronize()
+        assert torch.equal(spins, want)
+    # outside the capture the same handle allocates and goes on
+    psi.sweep(spins, seed=6, n_sweeps=2)
+    ref.sweep(want, seed=6, n_sweeps=2)
+    graph.replay()
+    ref.sweep(want, seed=5, n_sweeps=1)
+    torch.cuda.synchronize()
+    assert torch.equal(spins, want)
