@@ -99,6 +99,7 @@ __device__ __forceinline__ void samp_body(const ChainArgs& a, int bx, uint64_t s
   constexpr int SW = G::SW, NV = G::NV, MT = G::MT, NS = G::NS, KPL = CHI / 4;
   constexpr int NB = 16 * CG, ROW = kRowWords<CHI>;
   constexpr bool VAR = CKP && CG > 1;  // column groups may start and meet at bonds of their own
+  constexpr bool ONE = SW > 1 && !(CHI == 256 && CG == 2);  // a step is one piece of code
   constexpr int DU = NS > MT ? NS / MT : 1;             // steps of fragments in flight
   constexpr int UN = DU % 2 ? DU : DU / 2;              // pairs of steps unrolled
   static_assert(NS % MT == 0 || MT % NS == 0, "the ring divides a step, or steps the ring");
@@ -281,8 +282,17 @@ __device__ __forceinline__ void samp_body(const ChainArgs& a, int bx, uint64_t s
         win[cg] = side == 0 ? up : __brev(up) >> (31 - (k - lo));
       }
     };
-    // one step: out = this wave's tiles of (in times the walkers' slices)
-    auto step = [&](auto rnc, auto spc, auto dc, int i, const u32x4(&in)[CG][NV], u32x4(&out)[CG][MT]) {
+    // One step: out = this wave's tiles of (in times the walkers' slices).
+    // With several waves per side the ring is refilled inside the step, which
+    // then is one piece of code (ONE): with a copy for steps that renormalise
+    // (rn) and one for those that also keep the other slice's product (spl),
+    // the fragments in flight were moved to common registers where the copies
+    // met, and all of them waited for (BF16 bond 128, 10x10, 8192 walkers: 26.9
+    // -> 24.3 ms a sweep; FP8 bond 256, 8x8, 300 walkers: 11.9 -> 10.0 ms).
+    // Blocks of 32 at bond 256 keep the copies: their sums leave no room for
+    // the tests between tiles (9x9, two terms, 8192 walkers: 49.8 ms against 55.1).
+    auto step = [&](auto rnc, auto spc, auto dc, int i, bool rn, bool spl, const u32x4(&in)[CG][NV],
+                    u32x4(&out)[CG][MT]) {
       constexpr bool RN = decltype(rnc)::value, SPL = decltype(spc)::value;
       constexpr int DD = decltype(dc)::value;
       if constexpr (RN) {
@@ -293,10 +303,13 @@ __device__ __forceinline__ void samp_body(const ChainArgs& a, int bx, uint64_t s
 #pragma unroll
       for (int cg = 0; cg < CG; ++cg) {
         bit[cg] = (win[cg] >> (i % kRenormEvery)) & 1u;
+        psc[cg] = 1.f;
         if constexpr (RN) {
-          const int e = Op::row_exp(in[cg]);
-          psc[cg] = __builtin_amdgcn_ldexpf(1.f, -e);  // exact power of two
-          if (!VAR || (i >= s0[cg] && i < s1[cg])) ex[cg] += e;
+          if (!ONE || rn) {
+            const int e = Op::row_exp(in[cg]);
+            psc[cg] = __builtin_amdgcn_ldexpf(1.f, -e);  // exact power of two
+            if (!VAR || (i >= s0[cg] && i < s1[cg])) ex[cg] += e;
+          }
         }
       }
       // tile mt's products: acc[mt % 2]; the tile before is selected and split
@@ -309,14 +322,31 @@ __device__ __forceinline__ void samp_body(const ChainArgs& a, int bx, uint64_t s
       constexpr int OPT = Op::NCH * Op::OPC * 2 * CG;  // matrix ops per tile
       constexpr int NST = Op::kStages * CG;            // pieces of vector work per tile
       constexpr int OPCH = Op::OPC * 2 * CG, NPC = 2 * Op::kPieces;
-      f4 acc[2][2][CG];
+      // (sums of all tiles are kept where one test after them serves spl)
+      constexpr int NA = ONE && CG == 1 ? MT : 2;
+      f4 acc[NA][2][CG];
       typename Op::Operand x[2][2];
       typename Op::Post pst, psu;
       auto finish = [&](int mt, int st) {  // piece st of tile mt's vector work
-        const int cg = st / Op::kStages, q = st % Op::kStages, b = mt % 2;
+        const int cg = st / Op::kStages, q = st % Op::kStages, b = mt % NA;
         Op::template post<RN, MT>(q, pst, bit[cg], acc[b][0][cg], acc[b][1][cg], RN ? psc[cg] : 1.f, out[cg], mt);
         if constexpr (SPL)
           Op::template post<RN, MT>(q, psu, !bit[cg], acc[b][0][cg], acc[b][1][cg], psc[cg], oth[cg], mt);
+      };
+      // the other slice's product of tiles [lo, hi)
+      auto finish_other = [&](int lo, int hi) {
+        if constexpr (ONE) {
+          int f = spl;
+          asm("" : "+s"(f));  // (a test here, not a copy of the rest of the step)
+          if (f)
+#pragma unroll
+            for (int mt = lo; mt < hi; ++mt)
+#pragma unroll
+              for (int st = 0; st < NST; ++st) {
+                const int cg = st / Op::kStages, b = mt % NA;
+                Op::template post<RN, MT>(st % Op::kStages, psu, !bit[cg], acc[b][0][cg], acc[b][1][cg], psc[cg], oth[cg], mt);
+              }
+        }
       };
       auto frag = [&](int mt) -> Frag<E, KPL>(&)[2] { return S[(DD * MT + mt) % NS]; };
 #pragma unroll
@@ -330,7 +360,7 @@ __device__ __forceinline__ void samp_body(const ChainArgs& a, int bx, uint64_t s
 #pragma unroll
           for (int u = 0; u < OPCH; ++u) {
             const int kk = u / (2 * CG), sl = u / CG % 2, cg = u % CG;
-            f4& A = acc[mt % 2][sl][cg];
+            f4& A = acc[mt % NA][sl][cg];
             if (c == 0 && kk == 0) A = f4{0.f, 0.f, 0.f, 0.f};
             A = Op::op(x[xb][sl], in[cg], c, kk, A);
             // decode of the next chunk (of the next tile after the last one)
@@ -352,9 +382,11 @@ __device__ __forceinline__ void samp_body(const ChainArgs& a, int bx, uint64_t s
           load(frag(mt), i + (mt + NS) / MT, (mt + NS) % MT);
           hold_loads();
         }
+        if (NA == 2 && mt > 0) finish_other(mt - 1, mt);
       }
 #pragma unroll
       for (int st = 0; st < NST; ++st) finish(MT - 1, st);
+      finish_other(NA == 2 ? MT - 1 : 0, MT);
     };
     // fragments of the step DU - 1 ahead, into the slots of the last step (one
     // wave per side)
@@ -372,9 +404,11 @@ __device__ __forceinline__ void samp_body(const ChainArgs& a, int bx, uint64_t s
       if constexpr (VAR)
 #pragma unroll
         for (int cg = 0; cg < CG; ++cg) rn |= i == s0[cg];
-      if (!rn) step(std::false_type{}, std::false_type{}, dc, i, in, out);
-      else if (i == 0 && sp0 && side == 0) step(std::true_type{}, std::true_type{}, dc, i, in, out);
-      else step(std::true_type{}, std::false_type{}, dc, i, in, out);
+      const bool spl = i == 0 && sp0 && side == 0;
+      if constexpr (ONE) step(std::true_type{}, std::false_type{}, dc, i, rn, spl, in, out);
+      else if (!rn) step(std::false_type{}, std::false_type{}, dc, i, false, false, in, out);
+      else if (spl) step(std::true_type{}, std::true_type{}, dc, i, true, true, in, out);
+      else step(std::true_type{}, std::false_type{}, dc, i, true, false, in, out);
     };
     // after step i: the two extensions of the prefix, and checkpoints passed
     auto keep = [&](int i, const u32x4(&out)[CG][MT]) {
@@ -431,7 +465,7 @@ __device__ __forceinline__ void samp_body(const ChainArgs& a, int bx, uint64_t s
           // (only even steps renormalise)
           constexpr std::integral_constant<int, (U + 1) % DU> dc{};
           ahead(dc, i + U + 1);
-          step(std::false_type{}, std::false_type{}, dc, i + U + 1, o, r);
+          step(std::false_type{}, std::false_type{}, dc, i + U + 1, false, false, o, r);
           keep(i + U + 1, r);
           if (i + U + 2 >= n) more = false;
         };
@@ -473,8 +507,10 @@ __device__ __forceinline__ void samp_body(const ChainArgs& a, int bx, uint64_t s
       static_assert(DU <= 2, "one or two steps of fragments in flight");
       for (int i = 0; i < n; i += DU) {
         one(std::integral_constant<int, 0>{}, i);
-        if constexpr (DU > 1)
-          if (i + 1 < n) one(std::integral_constant<int, 1>{}, i + 1);
+        if constexpr (DU > 1) {
+          if (i + 1 >= n) break;  // (not a path back to the loop with fewer loads in flight)
+          one(std::integral_constant<int, 1>{}, i + 1);
+        }
       }
       for (int i = n; i < nmax; ++i) lds_barrier();
     }
