@@ -18,7 +18,7 @@ rtt_status launch_chain_as(const rttk::ChainArgs& a, int lds, hipStream_t s) {
   if (lds > (int)kLdsLimit) return fail(RTT_E_UNSUPPORTED, "sampler: %d bytes of LDS needed", lds);
   auto kfn = rttk::chain_kernel<D, CHI, CG, TW, CKP, CKG, PG>;
   HIPX(hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-  hipLaunchKernelGGL(kfn, dim3((a.W + 16 * CG - 1) / (16 * CG)), dim3(2 * rttk::SampGeo<D, CHI, CG>::SW * TW * 64),
+  hipLaunchKernelGGL(kfn, dim3((a.W + 16 * CG - 1) / (16 * CG)), dim3(2 * rttk::SampGeo<D, CHI, CG, TW>::SW * TW * 64),
                      lds, s, a);
   HIPX(hipGetLastError());
   return RTT_OK;
@@ -41,7 +41,7 @@ rtt_status launch_chain(const rttk::ChainArgs& a0, hipStream_t s) {
       if (sh.cg == 2) return launch_chain_as<D, CHI, 2, 1, false, false, false>(a, sh.lds, s);
     return launch_chain_as<D, CHI, 1, 1, false, false, false>(a, sh.lds, s);
   } else {
-    if constexpr (rttk::SampGeo<D, CHI>::SW == 1)
+    if constexpr (rttk::SampGeo<D, CHI, 1, 2>::SW == 1)
       if (sh.tw == 2) return launch_chain_as<D, CHI, 1, 2, true, false, false>(a, sh.lds, s);
     return launch_chain_as<D, CHI, 1, 1, true, false, false>(a, sh.lds, s);
   }

@@ -25,15 +25,21 @@
 namespace rttk {
 
 // Waves per side SW.  One where a step (both slices, all features) is short
-// enough for it: BF16 and FP8 up to bond 64 (32 matrix ops), FP32 up to 32.
-// FP32 matrix ops run at an eighth of the rate, so bond 64 uses four waves
-// (sweep of 4096 walkers at 8x8: 3.00 ms, with two 3.77) and 128 two (four
-// would halve the registers: 9.1 against 5.0 ms at 6x6, 1000 walkers).  BF16
-// and FP8 use two from 128 on, for 16 and 32 walkers alike: the waves' partial
-// dot products then meet in one order whatever the block's size.
-template <class D, int CHI, int CG = 1>
+// enough for it: BF16 and FP8 up to bond 64 (32 matrix ops), FP32 at 16.  FP32
+// matrix ops run at an eighth of the rate, so bond 64 uses four waves (sweep of
+// 4096 walkers at 8x8: 3.00 ms, with two 3.77) and 128 two (four would halve
+// the registers: 9.1 against 5.0 ms at 6x6, 1000 walkers).  Bond 32 uses two
+// (6x6, 1000 walkers: 0.45 ms, with one 0.54; in a batch, six states of 300 to
+// 365, 0.98 against 1.15), and one where two terms advance side by side (two
+// terms: 0.57 against 0.82).  BF16 and FP8 use two from 128 on, for 16 and 32
+// walkers alike: the waves' partial dot products then meet in one order
+// whatever the block's size.
+template <class D, int CHI, int CG = 1, int TW = 1>
 struct SampGeo {
-  static constexpr int SW = D::kF32 ? (CHI == 128 ? 2 : CHI == 64 ? 4 : 1) : (CHI >= 128 ? 2 : 1);
+  static constexpr int SW = D::kF32 ? (CHI == 128 ? 2 : CHI == 64 ? 4 : CHI == 32 && TW == 1 ? 2 : 1) : (CHI >= 128 ? 2 : 1);
+  // parts of a wave's dot product, added as the waves' are: as many in all at
+  // one bond, so that every shape of block gives the same bits
+  static constexpr int DP = D::kF32 && CHI == 32 ? 2 / SW : 1;
   static constexpr int NV = CHI / 16;  // tiles of a vector = 16-byte words per lane
   static constexpr int MT = NV / SW;   // output tiles per wave
   // fragment slots (tiles) in flight per wave: two steps up to bond 64 and
@@ -94,7 +100,7 @@ struct SampLayout {
 template <class D, int CHI, int CG, int TW, bool CKP, bool CKG, bool PG>
 __device__ __forceinline__ void samp_body(const ChainArgs& a, int bx, uint64_t sweep0) {
   using E = typename D::elem;
-  using G = SampGeo<D, CHI, CG>;
+  using G = SampGeo<D, CHI, CG, TW>;
   using Op = TileOp<D, CHI>;
   constexpr int SW = G::SW, NV = G::NV, MT = G::MT, NS = G::NS, KPL = CHI / 4;
   constexpr int NB = 16 * CG, ROW = kRowWords<CHI>;
@@ -336,7 +342,7 @@ __device__ __forceinline__ void samp_body(const ChainArgs& a, int bx, uint64_t s
       // the other slice's product of tiles [lo, hi)
       auto finish_other = [&](int lo, int hi) {
         if constexpr (ONE) {
-          int f = spl;
+          int f = __builtin_amdgcn_readfirstlane((int)spl);
           asm("" : "+s"(f));  // (a test here, not a copy of the rest of the step)
           if (f)
 #pragma unroll
@@ -558,9 +564,21 @@ __device__ __forceinline__ void samp_body(const ChainArgs& a, int bx, uint64_t s
             y[v] = xword(2 + pc, cg)[(wv * MT + v) * 64];
           }
         }
-        double s = Op::template dot<MT>(x, y);
-        s += __shfl_xor(s, 16);
-        s += __shfl_xor(s, 32);
+        double s = 0.0;
+#pragma unroll
+        for (int p = 0; p < G::DP; ++p) {
+          constexpr int PW = MT / G::DP;
+          u32x4 xp[PW], yp[PW];
+#pragma unroll
+          for (int v = 0; v < PW; ++v) {
+            xp[v] = x[p * PW + v];
+            yp[v] = y[p * PW + v];
+          }
+          double d = Op::template dot<PW>(xp, yp);
+          d += __shfl_xor(d, 16);
+          d += __shfl_xor(d, 32);
+          s = p == 0 ? d : s + d;
+        }
         if (g == 0) {
           const int wn = 16 * cg + m;
           fval[(t * SW + wv) * NB + wn] = s;
@@ -804,7 +822,7 @@ __device__ __forceinline__ void samp_body(const ChainArgs& a, int bx, uint64_t s
 }
 
 template <class D, int CHI, int CG, int TW, bool CKP, bool CKG = false, bool PG = false>
-__global__ void __launch_bounds__((2 * SampGeo<D, CHI, CG>::SW * TW * 64), (samp_min_waves<D, CHI>()))
+__global__ void __launch_bounds__((2 * SampGeo<D, CHI, CG, TW>::SW * TW * 64), (samp_min_waves<D, CHI>()))
     chain_kernel(ChainArgs a) {
   samp_body<D, CHI, CG, TW, CKP, CKG, PG>(a, blockIdx.x, a.sweep0);
 }

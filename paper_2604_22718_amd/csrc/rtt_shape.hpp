@@ -43,7 +43,7 @@ inline void chain_checkpoints(rttk::ChainArgs& a, int chi) {
 // LDS of a sampler block of this shape (persistent launches: no checkpoints)
 template <class D, int CHI>
 rttk::SampLayout samp_layout(const rttk::ChainArgs& a, int cg, int tw, bool ck_lds, bool p_lds) {
-  const int sw = cg == 2 ? rttk::SampGeo<D, CHI, 2>::SW : rttk::SampGeo<D, CHI, 1>::SW;
+  const int sw = cg == 2 ? rttk::SampGeo<D, CHI, 2>::SW : tw == 2 ? rttk::SampGeo<D, CHI, 1, 2>::SW : rttk::SampGeo<D, CHI>::SW;
   return rttk::SampLayout(CHI, a.T, (a.L + 63) / 64, a.nw, cg, sw, tw, a.n_ck, ck_lds, p_lds);
 }
 
@@ -57,8 +57,8 @@ inline bool two_groups(int W) { return W >= 32 * device_cus(); }
 // is decoded once for them (9x9, two FP8 terms, 8192 walkers: 80.6 ms a sweep
 // with 16 walkers per block before, 48.8 with 32).  A block of 32 takes more
 // LDS than the 16 walkers a state is accepted by: very long trains keep 16.
-// Up to bond 64, where one wave carries a whole vector, two terms of a
-// combination advance side by side.
+// Where one wave carries a whole vector, two terms of a combination advance
+// side by side.
 struct ChainShape {
   int cg, tw;
   bool p_global;
@@ -76,7 +76,7 @@ ChainShape chain_shape(const rttk::ChainArgs& a) {
       return s;
     }
   }
-  if (CHI <= 64 && rttk::SampGeo<D, CHI>::SW == 1 && a.T > 1) s.tw = 2;
+  if (rttk::SampGeo<D, CHI, 1, 2>::SW == 1 && a.T > 1) s.tw = 2;
   s.lds = samp_layout<D, CHI>(a, 1, s.tw, !kGlobal, true).total;
   return s;
 }
