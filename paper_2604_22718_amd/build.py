@@ -2,6 +2,8 @@
 import os
 import subprocess
 import sys
+import tempfile
+import threading
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -38,17 +40,20 @@ def _run(cmd, verbose):
 
 
 def build(verbose: bool = False) -> str:
-    objs = [os.path.join(CSRC, f"{name}.o") for name, _, _ in UNITS]
-    with ThreadPoolExecutor(len(UNITS)) as ex:
+    # objects in a directory of this build's own: several may run at once
+    with tempfile.TemporaryDirectory(prefix="librtt_") as tmp, ThreadPoolExecutor(len(UNITS)) as ex:
+        objs = [os.path.join(tmp, f"{name}.o") for name, _, _ in UNITS]
         jobs = [ex.submit(_run, [HIPCC, *FLAGS, *defs, "-c", os.path.join(CSRC, src), "-o", obj], verbose)
                 for (_, src, defs), obj in zip(UNITS, objs)]
         for j in jobs:
             j.result()
-    tmp = LIB + ".tmp"
-    _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-pthread", *objs, "-o", tmp], verbose)
-    for obj in objs:
-        os.remove(obj)
-    os.replace(tmp, LIB)
+        out = f"{LIB}.tmp{os.getpid()}_{threading.get_ident()}"   # beside the library: replaced in one step
+        try:
+            _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-pthread", *objs, "-o", out], verbose)
+            os.replace(out, LIB)
+        finally:
+            if os.path.exists(out):
+                os.remove(out)
     return LIB
 
 
