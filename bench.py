@@ -85,16 +85,21 @@ def baseline_sweep_rowsteps(pi, N, L):
     return len(first) + sum(L - f for f in first.values())
 
 
-# Sources that define or launch the matrix-core kernels, and the build flags:
-# counter figures taken on other versions of these are stale.  (The host
-# tensor-train algebra, the narrow-bond and the learned-proposal kernels
-# cannot change what the matrix-core kernels read and write.)
-KERNEL_SOURCES = ("csrc/rtt_device.hpp", "csrc/rtt_kernels.hpp", "csrc/rtt_chain.hpp", "csrc/rtt_tile.hpp", "csrc/rtt_lib.hip", "build.py")
+# Counter figures taken on other versions of the sources than these are stale:
+# the build flags and every file of csrc but the host tensor-train algebra, the
+# narrow-bond and the learned-proposal kernels, which cannot change what the
+# matrix-core kernels read and write.
+OTHER_SOURCES = ("rtt_tt.hpp", "rtt_narrow.hpp", "rtt_net.hpp")
+
+
+def kernel_sources():
+    files = sorted(os.listdir(os.path.join(ROOT, "paper_2604_22718_amd", "csrc")))
+    return [f"csrc/{f}" for f in files if f.endswith((".hip", ".hpp")) and f not in OTHER_SOURCES] + ["build.py"]
 
 
 def src_hash():
     h = hashlib.sha256()
-    for f in KERNEL_SOURCES:
+    for f in kernel_sources():
         h.update(open(os.path.join(ROOT, "paper_2604_22718_amd", f), "rb").read())
     return h.hexdigest()[:16]
 
