@@ -47,15 +47,19 @@ rttk::SampLayout samp_layout(const rttk::ChainArgs& a, int cg, int tw, bool ck_l
   return rttk::SampLayout(CHI, a.T, (a.L + 63) / 64, a.nw, cg, sw, tw, a.n_ck, ck_lds, p_lds);
 }
 
-// walkers from which a launch gives every compute unit 32 of them
-inline bool two_groups(int W) { return W >= 32 * device_cus(); }
+// More walkers than one block of 16 on every compute unit: at the bonds that
+// have both shapes a unit holds one block, and one round of 32 walkers is
+// shorter than two of 16 (a sweep of 6000 walkers: BF16 128, 10x10 R=3, 23.8
+// ms against 35.2; FP8 128, 8x8, 6.2 / 7.1; FP8 256, 9x9, two terms, 45.2 / 52.7;
+// FP32 128, 6x6, 8.4 / 8.4), but longer than one of 16 (4096 walkers: 17.7, 3.8,
+// 27.9 and 4.8 ms).
+inline bool two_groups(int W) { return W > 16 * device_cus(); }
 
 // The shape of a launch whose checkpoints are chosen: cg groups of 16 walkers
 // per block, tw terms side by side, prefixes in global memory or in LDS.
-// Bonds 128 and (FP8) 256 with enough walkers to give every CU a block of 32
-// run two column groups per block: each core fragment serves 32 walkers and
-// is decoded once for them (9x9, two FP8 terms, 8192 walkers: 80.6 ms a sweep
-// with 16 walkers per block before, 48.8 with 32).  A block of 32 takes more
+// Bonds 128 and (FP8) 256 run two column groups per block from two_groups
+// walkers on: each core fragment serves 32 walkers and is decoded once for
+// them.  A block of 32 takes more
 // LDS than the 16 walkers a state is accepted by: very long trains keep 16.
 // Where one wave carries a whole vector, two terms of a combination advance
 // side by side.

@@ -1,7 +1,8 @@
-"""FP8 cores at bond 256 with 32 walkers for every compute unit, where a block
-of 32 walkers keeps its prefixes in global memory: a train whose state fits 16
-walkers per block but not 32, and a first sweep inside a stream capture,
-which may not allocate for them."""
+"""Where the sampler's blocks change from 16 to 32 walkers: the first count past
+16 for every compute unit, and for FP8 cores at bond 256, whose blocks of 32
+keep their prefixes in global memory, a train whose state fits 16 walkers per
+block but not 32, and a first sweep inside a stream capture, which may not
+allocate for them."""
 import numpy as np
 import pytest
 import torch
@@ -62,3 +63,17 @@ def test_first_sweep_inside_a_capture(R):
     ref.sweep(want, seed=5, n_sweeps=1)
     torch.cuda.synchronize()
     assert torch.equal(spins, want)
+
+
+@pytest.mark.parametrize("chi,dtype,T", [(128, "f32", 1), (128, "bf16", 2), (128, "fp8", 1), (256, "fp8", 1), (256, "fp8", 2)])
+@pytest.mark.parametrize("past", [0, 1])
+def test_walkers_at_the_change_of_shape(R, chi, dtype, T, past):
+    W = 16 * torch.cuda.get_device_properties(0).multi_processor_count + past
+    print(f"[case] {dtype} bond {chi} T={T} W={W}", flush=True)
+    psi = make(R, 6, 2, chi, dtype, T, 820 + T)
+    bits = wl.random_spins(W, 6, 821)
+    for a, b in zip(chain(R, psi, bits, 2, 1), chain(R, psi, bits[:33], 2, 1)):   # (a walker's draws go by its index)
+        assert torch.equal(a[:33], b)
+    la, sg = psi.amplitudes(R.spins_to_device(wl.pack_spins(bits)))
+    lf, sf = psi.amplitudes(R.spins_to_device(wl.pack_spins(bits[-33:])))
+    assert torch.equal(la[-33:], lf) and torch.equal(sg[-33:], sf)
