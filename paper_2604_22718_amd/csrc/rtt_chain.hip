@@ -11,8 +11,6 @@ namespace {
 using namespace rtt_host;
 using Cores = rttk::RTT_CORES;
 
-constexpr int kDtype = rtt_host::kDtypeOf<Cores>;
-
 template <class D, int CHI, int CG, int TW, bool CKP, bool CKG, bool PG>
 rtt_status launch_chain_as(const rttk::ChainArgs& a, int lds, hipStream_t s) {
   if (lds > (int)kLdsLimit) return fail(RTT_E_UNSUPPORTED, "sampler: %d bytes of LDS needed", lds);

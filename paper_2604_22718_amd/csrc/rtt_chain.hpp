@@ -43,9 +43,11 @@ struct SampGeo {
   static constexpr int NV = CHI / 16;  // tiles of a vector = 16-byte words per lane
   static constexpr int MT = NV / SW;   // output tiles per wave
   // fragment slots (tiles) in flight per wave: two steps up to bond 64 and
-  // for 16 walkers at 128, else what the registers beside the vectors hold
-  // (a step of bond 256 is 256 or 512 matrix ops; eight slots there, or four
-  // of FP32 at 128, spill and take 2.4 times as long)
+  // for 16 walkers at 128, else about what the registers beside the vectors
+  // hold (a step of bond 256 is 256 or 512 matrix ops; eight slots there, or
+  // four of FP32 at 128, took 2.4 times as long).  Blocks of 32 at bond 256
+  // spill even with two, 752 bytes a lane, and are still the faster: 9x9, two
+  // terms, 50.7 ms a sweep of 8000 walkers against 56.2 in blocks of 16.
   static constexpr int NS = CHI <= 64 || (CHI == 128 && CG == 1 && !D::kF32) ? 2 * MT
                             : CHI == 128 ? (D::kF32 ? 2 : MT) : sizeof(typename D::elem) == 1 ? 4 / CG : 2;
 };

@@ -234,8 +234,8 @@ __device__ __forceinline__ void load_frag(Frag<E, KPL>& dst, const E* tile, int 
 // order the matrix ops take them, so that a wait for the first words does not
 // cover the last.  With two column groups a word lasts twice as long and
 // slice by slice is the better: 2 or 4 KB in a row for L2 (10x10, bond 128
-// BF16, 8192 walkers: 27.5 -> 27.0 ms a sweep; with one group, 32 walkers,
-// 11.8 against 11.9 ms).
+// BF16: R = 3, 8192 walkers, 24.0 against 24.2 ms a sweep; with one group, R = 2,
+// 32 walkers, 10.97 against 10.90).
 template <class E, int KPL, bool PAIR>
 __device__ __forceinline__ void load_frag2(Frag<E, KPL> (&dst)[2], const __attribute__((address_space(1))) char* tile0,
                                            const __attribute__((address_space(1))) char* tile1, int lane) {
@@ -291,21 +291,6 @@ __device__ __forceinline__ float group_sum(float x) {
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-// Max |x| over a row held by the four K-groups, then the power-of-two
-// exponent e with max * 2^-e in [0.5, 1).  Scaling by 2^-e is exact, so
-// renormalisation adds no rounding.
-template <int KPL>
-__device__ __forceinline__ int renorm_row(float (&v)[KPL]) {
-  float mx = 0.f;
-#pragma unroll
-  for (int c = 0; c < KPL; ++c) mx = fmaxf(mx, fabsf(v[c]));
-  mx = group_max(mx);
-  int e = (mx > 0.f) ? __builtin_amdgcn_frexp_expf(mx) : 0;
-#pragma unroll
-  for (int c = 0; c < KPL; ++c) v[c] = __builtin_amdgcn_ldexpf(v[c], -e);
-  return e;
-}
-
 // ---------------------------------------------------------------- activation rows
 // Act<D, CHI> keeps a row of CHI activations in LDS in the form the matrix
 // ops take, so that the wave producing a value converts it once instead of
@@ -341,12 +326,6 @@ struct Act<DF32, CHI> {
   __device__ __forceinline__ static void store1(float* row, int col, float x) { row[col] = x; }
   __device__ __forceinline__ static float get(const float* row, int i) { return row[i]; }
   __device__ __forceinline__ static void set_unit(float* row) { row[0] = 1.f; }
-  // the first dword of a stored unit vector e_0 (the rest are zero)
-  __device__ __forceinline__ static float unit_dword() { return 1.f; }
-  // copy the four activations at col..col+3 of a row
-  __device__ __forceinline__ static void copy4(float* dst, const float* src, int col) {
-    *reinterpret_cast<float4*>(dst + col) = *reinterpret_cast<const float4*>(src + col);
-  }
 };
 
 template <int CHI>
@@ -403,16 +382,6 @@ struct Act<DBF16, CHI> {
     *reinterpret_cast<uint2*>(p) = make_uint2(h01, h23);
     *reinterpret_cast<uint2*>(p + CHI) = make_uint2(l01, l23);
   }
-  // store4 through non-temporal stores (rows in global memory)
-  __device__ __forceinline__ static void store4_nt(float* row, int col, f4 v) {
-    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-    uint32_t h01, l01, h23, l23;
-    split_bf16x2(v[0], v[1], h01, l01);
-    split_bf16x2(v[2], v[3], h23, l23);
-    uint16_t* p = hi(row) + col;
-    __builtin_nontemporal_store(u2{h01, h23}, reinterpret_cast<u2*>(p));
-    __builtin_nontemporal_store(u2{l01, l23}, reinterpret_cast<u2*>(p + CHI));
-  }
   __device__ __forceinline__ static void store1(float* row, int col, float x) {
     uint16_t h, l;
     split(x, h, l);
@@ -423,13 +392,6 @@ struct Act<DBF16, CHI> {
     return bf16_to_f32(hi(row)[i]) + bf16_to_f32(hi(row)[CHI + i]);
   }
   __device__ __forceinline__ static void set_unit(float* row) { hi(row)[0] = 0x3F80u; }
-  // the first dword of a stored unit vector e_0: hi[0] = 1, hi[1] = 0
-  __device__ __forceinline__ static float unit_dword() { return __uint_as_float(0x3F80u); }
-  // copy the four activations at col..col+3 of a row (hi and lo parts)
-  __device__ __forceinline__ static void copy4(float* dst, const float* src, int col) {
-    *reinterpret_cast<uint2*>(hi(dst) + col) = *reinterpret_cast<const uint2*>(hi(src) + col);
-    *reinterpret_cast<uint2*>(hi(dst) + CHI + col) = *reinterpret_cast<const uint2*>(hi(src) + CHI + col);
-  }
 };
 
 // FP8 cores take the same activation rows as BF16 cores

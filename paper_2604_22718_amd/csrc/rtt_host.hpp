@@ -72,8 +72,10 @@ inline size_t pass_lds_bytes(int chi, int nslot, int nw, int dtype) {
   return (size_t)wpb * (nb * nslot * rs * 4 + nb * nslot * 4 + nw * 8);
 }
 
-// Passes whose rows stay in the registers of one wave per walker: at bond 32
-// always (8x8, BF16 evaluation: 16 walkers 160 -> 147 us, 4096 472 -> 328 us);
+// Passes whose rows stay in the registers of one wave per walker, where a
+// group's schedule has no more rows than that holds (up to 79 spins, or 159 in
+// two groups; more take the rows-in-LDS form): at bond 32 for any number of
+// walkers (8x8, BF16 evaluation: 16 walkers 160 -> 147 us, 4096 472 -> 328 us);
 // at bond 64 from a pass per SIMD, where the rows-in-LDS form's four waves per
 // walker queue for the chip (8x8: 1024 walkers 316 -> 250 us, 4096 941 -> 615
 // us; below that a lone wave's chain of steps is the longer, 512 walkers 191
@@ -87,8 +89,10 @@ inline size_t pass_wave_lds(int dtype, int chi) { return rttk::pass_wave_lds(chi
 inline int pass_walkers(int chi, bool wave) { return wave ? 4 : 4 / rttk_wpw(chi); }
 
 // Sampler tile of a class: 16 walkers per block, or 32 (two column groups
-// sharing every core fragment) at the bonds where that kernel fits in
-// registers (at 64 and 256 the second group's operands spill).
+// sharing every core fragment) at bonds 32 and 128.  At 64 the second group
+// spilled when vectors were in LDS (with vectors in registers it was not tried),
+// and at 256 the prefixes of 32 do not fit in LDS (a single state keeps them in
+// global memory).
 constexpr bool batch_cg2(int chi) { return chi == 32 || chi == 128; }
 
 // One class of a batch as its persistent kernels are launched

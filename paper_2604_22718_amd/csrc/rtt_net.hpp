@@ -43,22 +43,16 @@ struct NetGeo {
   }
 };
 
-// One 3x3 layer for this thread's site: acc[co] = b[co] + sum W[co][ci][t] in(ci, nb[t]).
-// in_act: whether the input buffer holds pre-activations (SiLU applied on read).
-template <int CI>
-__device__ __forceinline__ void conv_site(const float* __restrict__ W, const float* __restrict__ b,
-                                          const float* in, bool in_act, const NetGeo& g,
-                                          float (&acc)[kNetC]) {
+// The first layer (one input channel) for this thread's site: acc[co] = b[co] + sum W[co][t] z(nb[t]).
+__device__ __forceinline__ void conv_site(const float* __restrict__ W, const float* __restrict__ b, const float* z,
+                                          const NetGeo& g, float (&acc)[kNetC]) {
 #pragma unroll
   for (int co = 0; co < kNetC; ++co) acc[co] = b[co];
-  for (int ci = 0; ci < CI; ++ci) {
 #pragma unroll
-    for (int t = 0; t < 9; ++t) {
-      float x = in[ci * g.N + g.nb[t]];
-      if (in_act) x = silu_f(x);
+  for (int t = 0; t < 9; ++t) {
+    const float x = z[g.nb[t]];
 #pragma unroll
-      for (int co = 0; co < kNetC; ++co) acc[co] = fmaf(W[(co * CI + ci) * 9 + t], x, acc[co]);
-    }
+    for (int co = 0; co < kNetC; ++co) acc[co] = fmaf(W[co * 9 + t], x, acc[co]);
   }
 }
 
@@ -177,7 +171,7 @@ __device__ inline float* net_forward_mfma(const float* __restrict__ P, const uin
   __syncthreads();
   if (act) {
     float acc[kNetC];
-    conv_site<1>(P + oW1, P + ob1, z, false, g, acc);
+    conv_site(P + oW1, P + ob1, z, g, acc);
     const size_t plane = (size_t)NP * kNetC;
 #pragma unroll
     for (int c = 0; c < kNetC; c += 2) {
@@ -437,9 +431,9 @@ struct NetGradArgs {
 
 // Gradient of sum_b coef_b log q(c_b, k_b | s_b), coef_b = -(a_b k_b - baseline)
 // / B, on the FP32 matrix cores.  A block takes samples b, b + gridDim, ... and
-// keeps its sums of the weight gradients in registers over all of them; one
-// partial gradient per block then goes to memory (a gradient per sample was
-// 313 MB written and read back at 4096 samples).
+// sums their weight gradients; one partial gradient per block then goes to
+// memory (a gradient per sample was 313 MB written and read back at 4096
+// samples).
 //   conv layers and their transposes: out[ch][site], 16 x 16 tiles, K = 9 taps
 //     x 32 channels;
 //   weight gradients: dW[co][ci][t] = sum_i da[co][i] h[ci][nb(i, t)], wave
@@ -450,7 +444,9 @@ struct NetGradArgs {
 // Buffers: X0 a1 -> da1; X1 h1 -> a3 -> da3; X2 a2 -> da2; X3 h2 -> h1.
 // Matrix ops of 4096 samples at 10x10 take 330 us of all 1024 SIMDs; measured
 // 0.99 ms (one thread per site or weight, a gradient per sample: 3.5 ms with
-// the sum over samples), the rest being layer weights, LDS reads and barriers.
+// the sum over samples), the rest being layer weights, LDS reads, barriers and
+// scratch: the 72 weights a lane holds in a layer and the 72 sums of a sample
+// leave no room for the block's sums, which spill (796 bytes a lane).
 __device__ __forceinline__ int gidx(int site, int ch) {
   return site * kNetC + ((((ch >> 2) ^ (site >> 1)) & 7) << 2) + (ch & 3);
 }

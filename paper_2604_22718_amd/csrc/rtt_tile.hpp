@@ -145,7 +145,8 @@ struct TileOp<DFP8, CHI> : TileOp<DBF16, CHI> {
   }
 };
 
-// element i of a table no kernel writes, at a wave-uniform index: a scalar load
+// element i of a table that is not written while the kernel runs, at a
+// wave-uniform index: a scalar load
 template <class V>
 __device__ __forceinline__ V uniform_load(const V* p, long long i) {
   typedef const __attribute__((address_space(4))) V* cptr;
