@@ -46,7 +46,7 @@ struct SampGeo {
   // for 16 walkers at 128, else about what the registers beside the vectors
   // hold (a step of bond 256 is 256 or 512 matrix ops; eight slots there, or
   // four of FP32 at 128, took 2.4 times as long).  Blocks of 32 at bond 256
-  // spill even with two, 752 bytes a lane, and are still the faster: 9x9, two
+  // spill even with two, 736 bytes a lane, and are still the faster: 9x9, two
   // terms, 50.7 ms a sweep of 8000 walkers against 56.2 in blocks of 16.
   static constexpr int NS = CHI <= 64 || (CHI == 128 && CG == 1 && !D::kF32) ? 2 * MT
                             : CHI == 128 ? (D::kF32 ? 2 : MT) : sizeof(typename D::elem) == 1 ? 4 / CG : 2;
@@ -311,7 +311,7 @@ __device__ __forceinline__ void samp_body(const ChainArgs& a, int bx, uint64_t s
 #pragma unroll
       for (int cg = 0; cg < CG; ++cg) {
         bit[cg] = (win[cg] >> (i % kRenormEvery)) & 1u;
-        psc[cg] = 1.f;
+        if constexpr (ONE) psc[cg] = 1.f;
         if constexpr (RN) {
           if (!ONE || rn) {
             const int e = Op::row_exp(in[cg]);
@@ -412,10 +412,9 @@ __device__ __forceinline__ void samp_body(const ChainArgs& a, int bx, uint64_t s
       if constexpr (VAR)
 #pragma unroll
         for (int cg = 0; cg < CG; ++cg) rn |= i == s0[cg];
-      const bool spl = i == 0 && sp0 && side == 0;
-      if constexpr (ONE) step(std::true_type{}, std::false_type{}, dc, i, rn, spl, in, out);
+      if constexpr (ONE) step(std::true_type{}, std::false_type{}, dc, i, rn, i == 0 && sp0 && side == 0, in, out);
       else if (!rn) step(std::false_type{}, std::false_type{}, dc, i, false, false, in, out);
-      else if (spl) step(std::true_type{}, std::true_type{}, dc, i, true, true, in, out);
+      else if (i == 0 && sp0 && side == 0) step(std::true_type{}, std::true_type{}, dc, i, true, true, in, out);
       else step(std::true_type{}, std::false_type{}, dc, i, true, false, in, out);
     };
     // after step i: the two extensions of the prefix, and checkpoints passed
