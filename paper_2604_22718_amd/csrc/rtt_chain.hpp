@@ -320,7 +320,7 @@ __device__ __forceinline__ void samp_body(const ChainArgs& a, int bx, uint64_t s
           }
         }
       }
-      // tile mt's products: acc[mt % 2]; the tile before is selected and split
+      // tile mt's products: acc[mt % NA]; the tile before is selected and split
       // between its matrix ops, and each chunk decoded during the one before
       // The written order is held only with FP8 codes at bond 256, where the
       // decode fills the matrix ops' shadow (9x9, two terms, 8192 walkers:
