@@ -24,7 +24,8 @@
  *     sampling calls only enqueue work on it and never synchronise; create,
  *     lincomb and destroy synchronise the device.  Workspace a call needs
  *     beyond what a handle already holds (flip-ratio rows for more walkers
- *     than any earlier call, proposal buffers) comes from HIP's
+ *     than any earlier call, proposal buffers, sampler vectors of FP8 states
+ *     at bond 256) comes from HIP's
  *     stream-ordered allocator on `stream`, which does not synchronise
  *     either; a handle's workspace is used by one stream at a time, so calls
  *     on one handle (RTT or network) must not overlap on different streams.
